@@ -156,6 +156,22 @@ double *static_scratch(int dev)
     return g_static_ptr[dev];
 }
 
+// The kernels' launch attributes on device dev (which must be current), set
+// by the first handle on it; they do not depend on the handle.
+std::mutex g_prepare_mu;
+bool g_prepared[kMaxDevices] = {};
+
+bool prepare_once(int dev, const rtk::DeviceLimits &lim)
+{
+    std::lock_guard<std::mutex> lk(g_prepare_mu);
+    if (dev >= 0 && dev < kMaxDevices && g_prepared[dev]) return true;
+    if (rtk::prepare_kernels(lim) != hipSuccess || rtk::prepare_stream_kernels(lim) != hipSuccess ||
+        rtk::prepare_deep_kernels(lim) != hipSuccess)
+        return false;
+    if (dev >= 0 && dev < kMaxDevices) g_prepared[dev] = true;
+    return true;
+}
+
 }  // namespace
 
 struct rt_handle {
@@ -356,8 +372,7 @@ extern "C" rt_status rt_create(const rt_config *cfg, rt_handle **out)
         }
         h->dev.n_cu = n_cu;
         h->dev.lds = (size_t)lds;
-        if (rtk::prepare_kernels(h->dev) != hipSuccess ||
-            rtk::prepare_deep_kernels(h->dev) != hipSuccess) {
+        if (!prepare_once(cfg->device, h->dev)) {
             delete h;
             return RT_EDEVICE;
         }
@@ -450,8 +465,22 @@ static rtk::Geometry request_geometry(const rt_handle *h, const rt_request *r)
         (r->kernel == RT_KERNEL_AUTO && r->cols_per_block == 0 && prefer_deep(h, r->n_cols, N)))
         return rtk::deep_geometry(r->n_cols, N, h->NBG, h->dev);
     const int kernel = r->kernel == RT_KERNEL_LANE ? rtk::KERNEL_LANE : rtk::KERNEL_LAYER;
-    return rtk::solve_geometry(r->n_cols, N, h->NBG, r->cols_per_block, kernel, r->precision,
-                               h->dev, h->NG);
+    const rtk::Geometry g = rtk::solve_geometry(r->n_cols, N, h->NBG, r->cols_per_block, kernel,
+                                                r->precision, h->dev, h->NG);
+    if (kernel == rtk::KERNEL_LANE || r->cols_per_block != 0 || g.threads == 0) return g;
+    rtk::Geometry gs = rtk::stream_geometry(r->n_cols, N, h->NBG, h->NG, r->precision == RT_MIXED, h->dev);
+    if (gs.threads == 0) return g;
+    gs.scratch = g.scratch;   // the layer kernel's reservation, which holds the same records
+    return gs;
+}
+
+static hipError_t launch(const rtk::SolveArgs &a, const rtk::Geometry &g, int precision, hipStream_t s)
+{
+    switch (g.kernel) {
+    case rtk::KERNEL_DEEP: return rtk::launch_deep(a, g, precision, s);
+    case rtk::KERNEL_STREAM: return rtk::launch_stream(a, g, precision, s);
+    default: return rtk::launch_solve(a, g, precision, s);
+    }
 }
 
 static rt_status validate(rt_handle *h, const rt_request *r)
@@ -682,9 +711,7 @@ extern "C" rt_status rt_solve_fluxes(rt_handle *h, const rt_request *r, void *st
         h->scratch_bytes = need;
     }
     rtk::SolveArgs a = make_args(h, r, h->d_scratch);
-    hipError_t e = g.kernel == rtk::KERNEL_DEEP
-                       ? rtk::launch_deep(a, g, r->precision, (hipStream_t)stream)
-                       : rtk::launch_solve(a, g, r->precision, (hipStream_t)stream);
+    hipError_t e = launch(a, g, r->precision, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(h, e, "solve launch");
     return RT_OK;
 }
@@ -702,9 +729,7 @@ extern "C" rt_status rt_solve_fluxes_noalloc(rt_handle *h, const rt_request *r, 
     // the kernels write every word of the work buffer they read later, so it
     // needs no clearing between calls
     rtk::SolveArgs a = make_args(h, r, h->static_ws);
-    hipError_t e = g.kernel == rtk::KERNEL_DEEP
-                       ? rtk::launch_deep(a, g, r->precision, (hipStream_t)stream)
-                       : rtk::launch_solve(a, g, r->precision, (hipStream_t)stream);
+    hipError_t e = launch(a, g, r->precision, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(h, e, "solve launch");
     return RT_OK;
 }
@@ -1006,13 +1031,17 @@ static void pump(rt_handle *h)
             continue;
         }
         int blocks = 0;
+        rtk::Geometry gb = g0;
         for (auto it = h->queued.begin(); it != h->queued.end() && (int)b.jobs.size() < kMaxBatch;) {
-            // one launch shape per batch: same kernel, precision, input storage, tile,
-            // threads and LDS
+            // one launch shape per batch: same kernel, precision, input storage and
+            // threads; the layer and lane kernels also need the same tile and LDS
+            // (a stream workgroup takes its layout from its own request, within
+            // the largest LDS of the batch)
+            const bool stream = g0.kernel == rtk::KERNEL_STREAM;
             if (it->req.precision != prec || it->req.input_dtype != in32 ||
-                it->g.kernel != g0.kernel || it->g.K != g0.K ||
-                it->g.threads != g0.threads || it->g.lds != g0.lds || it->g.PC != g0.PC ||
-                it->g.CH != g0.CH) {
+                it->g.kernel != g0.kernel || it->g.threads != g0.threads ||
+                (!stream && (it->g.K != g0.K || it->g.lds != g0.lds || it->g.PC != g0.PC ||
+                             it->g.CH != g0.CH))) {
                 ++it;
                 continue;
             }
@@ -1026,6 +1055,7 @@ static void pump(rt_handle *h)
             a.CH = j.g.CH;
             a.L = j.g.lanes;
             a.status = b.d_status + b.jobs.size();
+            gb.lds = std::max(gb.lds, j.g.lds);
             b.h_args[b.jobs.size()] = a;
             b.h_first[b.jobs.size()] = blocks;
             blocks += j.g.blocks;
@@ -1040,7 +1070,9 @@ static void pump(rt_handle *h)
             e = hipMemcpyAsync(b.d_first, b.h_first, sizeof(int) * n, hipMemcpyHostToDevice, s);
         if (e == hipSuccess) e = hipMemsetAsync(b.d_status, 0, sizeof(uint32_t) * n, s);
         if (e == hipSuccess)
-            e = rtk::launch_solve_batch(b.d_args, b.d_first, n, blocks, g0, prec, in32, s);
+            e = gb.kernel == rtk::KERNEL_STREAM
+                    ? rtk::launch_stream_batch(b.d_args, b.d_first, n, blocks, gb, prec, in32, s)
+                    : rtk::launch_solve_batch(b.d_args, b.d_first, n, blocks, gb, prec, in32, s);
         if (e == hipSuccess)
             e = hipMemcpyAsync(b.h_status, b.d_status, sizeof(uint32_t) * n, hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipEventRecord(b.done, s);
@@ -1080,7 +1112,8 @@ extern "C" rt_status rt_submit(rt_handle *h, const rt_request *r, uint64_t *tick
     // the persistent worker takes layer-kernel requests with FP64 input storage;
     // the others (deep and lane kernels, FP32 inputs) run as batched launches
     bool worker = false;
-    if (h->cfg.serve_mode == RT_SERVE_PERSISTENT && !h->wbroken && j.g.kernel == rtk::KERNEL_LAYER &&
+    if (h->cfg.serve_mode == RT_SERVE_PERSISTENT && !h->wbroken &&
+        (j.g.kernel == rtk::KERNEL_LAYER || j.g.kernel == rtk::KERNEL_STREAM) &&
         r->input_dtype == RT_F64) {
         const rtk::Geometry gw = rtk::worker_geometry(r->n_cols, request_slabs(r), h->NBG, r->precision,
                                                       h->dev, h->NG);

@@ -21,6 +21,8 @@ enum Kernel : int {
                         // shared by the workgroup; only the elimination is per lane
     KERNEL_DEEP = 3,    // a column's layers split into segments on separate
                         // workgroups, the recurrences composed per segment
+    KERNEL_STREAM = 4,  // a wavefront owns 64 lanes for the whole sweep (the layer
+                        // kernel's default tile on grids that fill the chip)
 };
 
 // Everything one solve kernel needs (passed by value).
@@ -125,6 +127,12 @@ constexpr int kMaxTileLanes = 1024;    // (column, bin) lanes of one layer-kerne
 Geometry solve_geometry(int C, int N, int NB, int K, int kernel, int precision,
                         const DeviceLimits &dev, int NG = 1);
 hipError_t launch_solve(const SolveArgs &a, const Geometry &g, int precision, hipStream_t s);
+// Wavefront-per-lanes solve (threads = 0: the shape does not fit it).
+Geometry stream_geometry(int C, int N, int NB, int NG, bool mixed, const DeviceLimits &dev);
+hipError_t launch_stream(const SolveArgs &a, const Geometry &g, int precision, hipStream_t s);
+hipError_t launch_stream_batch(const SolveArgs *d_reqs, const int *d_first, int n, int total_blocks,
+                               const Geometry &g, int precision, int in_f32, hipStream_t s);
+hipError_t prepare_stream_kernels(const DeviceLimits &dev);
 // Layer-parallel path for deep columns (several launches on stream s): K =
 // segments per column, PC = slabs per segment; scratch sized for it.
 Geometry deep_geometry(int C, int N, int NB, const DeviceLimits &dev);
