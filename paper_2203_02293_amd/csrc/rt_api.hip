@@ -1036,10 +1036,12 @@ static void pump(rt_handle *h)
             // one launch shape per batch: same kernel, precision, input storage and
             // threads; the layer and lane kernels also need the same tile and LDS
             // (a stream workgroup takes its layout from its own request, within
-            // the largest LDS of the batch)
+            // the largest LDS of the batch; columns in one piece and in segments are
+            // different kernels)
             const bool stream = g0.kernel == rtk::KERNEL_STREAM;
             if (it->req.precision != prec || it->req.input_dtype != in32 ||
                 it->g.kernel != g0.kernel || it->g.threads != g0.threads ||
+                (stream && (it->g.PC > 1) != (g0.PC > 1)) ||
                 (!stream && (it->g.K != g0.K || it->g.lds != g0.lds || it->g.PC != g0.PC ||
                              it->g.CH != g0.CH))) {
                 ++it;
@@ -1071,7 +1073,7 @@ static void pump(rt_handle *h)
         if (e == hipSuccess) e = hipMemsetAsync(b.d_status, 0, sizeof(uint32_t) * n, s);
         if (e == hipSuccess)
             e = gb.kernel == rtk::KERNEL_STREAM
-                    ? rtk::launch_stream_batch(b.d_args, b.d_first, n, blocks, gb, prec, in32, s)
+                    ? rtk::launch_stream_batch(b.d_args, b.d_first, n, blocks, gb, h->NBG, prec, in32, s)
                     : rtk::launch_solve_batch(b.d_args, b.d_first, n, blocks, gb, prec, in32, s);
         if (e == hipSuccess)
             e = hipMemcpyAsync(b.h_status, b.d_status, sizeof(uint32_t) * n, hipMemcpyDeviceToHost, s);

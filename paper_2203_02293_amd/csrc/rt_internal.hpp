@@ -131,7 +131,7 @@ hipError_t launch_solve(const SolveArgs &a, const Geometry &g, int precision, hi
 Geometry stream_geometry(int C, int N, int NB, int NG, bool mixed, const DeviceLimits &dev);
 hipError_t launch_stream(const SolveArgs &a, const Geometry &g, int precision, hipStream_t s);
 hipError_t launch_stream_batch(const SolveArgs *d_reqs, const int *d_first, int n, int total_blocks,
-                               const Geometry &g, int precision, int in_f32, hipStream_t s);
+                               const Geometry &g, int NB, int precision, int in_f32, hipStream_t s);
 hipError_t prepare_stream_kernels(const DeviceLimits &dev);
 // Layer-parallel path for deep columns (several launches on stream s): K =
 // segments per column, PC = slabs per segment; scratch sized for it.

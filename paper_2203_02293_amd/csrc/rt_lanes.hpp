@@ -1,0 +1,200 @@
+// rt_lanes.hpp -- what the wavefront-per-lanes kernels share (device code):
+// the layout of columns over a wavefront's lanes, Planck radiances from edge
+// integrals in LDS, and the outputs of a workgroup's columns from its level sums.
+#pragma once
+
+#include "rt_internal.hpp"
+#include "rt_math.hpp"
+#include "rt_physics.hpp"
+#include "rt_planck.hpp"
+#include "rt_wave.hpp"
+
+#include <type_traits>
+
+namespace rtk {
+
+// This source file's copy of the Planck table on each device (filled by
+// upload_planck_table before the device's first launch from the file).
+static __device__ __attribute__((aligned(16))) double planck_values[kPlanckTable];
+
+static hipError_t upload_planck_table()
+{
+    static double host[kPlanckTable];
+    static const bool built = (planck_table(host), true);
+    (void)built;
+    return hipMemcpyToSymbol(HIP_SYMBOL(planck_values), host, sizeof host);
+}
+
+// Planck edge integral at x (planck_edge's sign convention); tab: the table in LDS (FP64).
+template <class R>
+__device__ __forceinline__ R edge_integral(double x, const double *tab)
+{
+    if constexpr (sizeof(R) == 8) return planck_lookup(x, tab);
+    else return planck_edge<R>(x);
+}
+
+// n / d for 0 <= n < 2^20, 0 < d (no integer division)
+__device__ __forceinline__ int small_div(int n, int d)
+{
+    return (int)(((float)n + 0.5f) * (1.0f / (float)d));
+}
+
+// Lane layout of a problem over wavefronts: up to 64 lanes per column, gw columns
+// per wavefront, each padded to NBp lanes (a power of two from 8 to 64); or a wider
+// column over NBw wavefronts, slices of NBs lanes each (the last one may hold fewer).
+struct LaneLayout {
+    int NBp, gw, NBw, NBs;
+};
+__host__ __device__ __forceinline__ LaneLayout lane_layout(int NB)
+{
+    LaneLayout l;
+    int p = 8;
+    while (p < NB && p < 64) p *= 2;
+    l.NBp = p;
+    l.gw = NB > 64 ? 1 : 64 / p;
+    l.NBw = (NB + 63) / 64;
+    l.NBs = (NB + l.NBw - 1) / l.NBw;
+    return l;
+}
+
+// Planck edges that one wavefront needs at most: its lanes' bins and one more.
+__host__ __device__ __forceinline__ int wave_edges(int NB, int NG)
+{
+    const int NBR = NB / NG, NBs = lane_layout(NB).NBs;
+    const int most = NG == 1 ? NBs : (NBs + NG - 2) / NG + 1;
+    return (most < NBR ? most : NBR) + 1;
+}
+
+// base + off bytes: a wavefront-uniform base and a 32-bit offset per lane
+template <class T>
+__device__ __forceinline__ T &at(T *base, unsigned off)
+{
+    return *reinterpret_cast<T *>(reinterpret_cast<char *>(const_cast<typename std::remove_const<T>::type *>(base)) + off);
+}
+
+// A wavefront-uniform value kept in scalar registers from here on (not read
+// again from memory at its uses).
+template <class T>
+__device__ __forceinline__ void uniform_value(T &x)
+{
+    asm volatile("" : "+s"(x));
+}
+
+// The options used per layer, read anew here and kept in scalar registers.
+__device__ __forceinline__ Opts uniform_options(ArgsK ap)
+{
+    Opts o = ((const SolveArgs *)ap)->o;
+    uniform_value(o.e_tau);
+    uniform_value(o.g_guard);
+    uniform_value(o.improved);
+    uniform_value(o.noniso);
+    uniform_value(o.e_clamp);
+    return o;
+}
+
+// LDS values written by lanes of this wavefront are read by others of it.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Temperature of level l of column cc: on the sub-layer grid even levels are
+// interfaces and odd levels layer centres.
+__device__ __forceinline__ double level_T(const SolveArgs &a, bool sub, int l, int cc)
+{
+    const double *T_if = a.T, *T_ce = sub ? a.Tc : a.T;
+    const double *base = (sub && (l & 1)) ? T_ce : T_if;
+    return base[(long long)(sub ? (l >> 1) : l) * a.C + cc];
+}
+
+// Bin radiance at temperature Td from the edge integrals re[0], re[1] of the
+// bin; c2b, c2a: c2 / lambda at its edges (LDS), fb, fa the same in FP32.
+template <bool MIXED, class R>
+__device__ __forceinline__ R bin_radiance(const R *re, double Td, float fb, float fa, const double *c2)
+{
+    const R Tr = R(Td), T2 = Tr * Tr;
+    R I = planck_combine<R>(re[0], re[1]);
+    if constexpr (MIXED) {
+        const R iT = rcp(Tr);
+        const R xb = fb * iT, xa = fa * iT;
+        if (planck_narrow(xa, xb)) {
+            const double iTd = rcp(Td);
+            I = planck_gl3(c2[1] * iTd, c2[0] * iTd);
+        }
+    }
+    return R(kPref) * T2 * T2 * I;
+}
+
+// Workgroup of request r with first[r] <= g < first[r+1] (batched launches).
+__device__ __forceinline__ int batch_request(const int *first, int n, int g)
+{
+    int lo = 0, hi = n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (first[mid] <= g) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// Outputs of the K columns from c0 on from their level sums, sum(level, 0: up, 1:
+// down or 2: beam, column): the bin-summed fluxes, the net flux, the heating and the
+// flags.  All threads of the workgroup; the sums and s_flag [K] are complete.
+template <class Sum>
+__device__ __forceinline__ void write_columns(ArgsK ap, int c0, int K, uint32_t *s_flag, Sum sum)
+{
+    opaque_args(ap);
+    auto args = [&]() -> const SolveArgs & { return *(const SolveArgs *)ap; };
+    const int C = args().C, N = args().N;
+    const bool sub = args().sub != 0;
+    const int tid = threadIdx.x;
+    auto out_at = [&](double *iface, double *centre, int l, int cc) -> double * {
+        if (sub) return ((l & 1) ? centre : iface) + (long long)(l >> 1) * C + cc;
+        return iface + (long long)l * C + cc;
+    };
+    for (int t = tid; t < (N + 1) * K; t += blockDim.x) {
+        const int lev = K == 1 ? t : small_div(t, K), k = t - lev * K, cc = c0 + k;
+        if (cc >= C) continue;
+        const bool dk = args().mu[cc] > 0.0;   // (night columns have no beam sums)
+        auto net = [&](int l, double &su, double &sd, double &sb) -> double {
+            su = sum(l, 0, k);
+            sd = sum(l, 1, k);
+            sb = dk ? sum(l, 2, k) : 0.0;
+            return su - sd - sb;
+        };
+        double su, sd, sb, x, y, z;
+        const double fn = net(lev, su, sd, sb);
+        *out_at(args().F_up, args().F_up_c, lev, cc) = su;
+        *out_at(args().F_dn, args().F_dn_c, lev, cc) = sd;
+        *out_at(args().F_beam, args().F_beam_c, lev, cc) = sb;
+        *out_at(args().F_net, args().F_net_c, lev, cc) = fn;
+        if (!isfinite(fn)) atomicOr(&s_flag[k], (uint32_t)F_NONFIN);
+        const int up = sub ? lev + 2 : lev + 1;   // the interface above
+        if (up > N || (sub && (lev & 1))) continue;
+        const int j = sub ? lev >> 1 : lev;
+        const double fnu = net(up, x, y, z);
+        const long long o = (long long)j * C + cc;
+        const double p0 = args().p[o], p1 = args().p[o + C];
+        const double dp = p0 - p1;
+        bool bad = !(dp > 0.0);
+        if (sub) {
+            const double pm = args().pc[o];
+            bad = bad || !(p0 > pm && pm > p1);
+        }
+        if (bad) atomicOr(&s_flag[k], (uint32_t)F_INVALID);
+        const double qh = args().o.gravity * (fn - fnu) / dp;
+        args().heat[o] = qh;
+        if (args().dTdt) args().dTdt[o] = qh / args().o.cp;
+    }
+    __syncthreads();
+    for (int k = tid; k < K; k += blockDim.x) {
+        if (c0 + k >= C) continue;
+        if (args().flags) args().flags[c0 + k] = s_flag[k];
+        const uint32_t bad = status_bits(s_flag[k]);
+        if (args().status && bad) atomicOr(args().status, bad);
+    }
+}
+
+}  // namespace rtk

@@ -1,22 +1,34 @@
-// rt_stream.hip -- the wavefront-per-lanes solve for grids that fill the chip.
+// rt_stream.hip -- the wavefront-per-lanes solve: the default tile of the layer
+// kernel.
 //
 // Paper: Deitrick et al., "The THOR+HELIOS general circulation model"
 // (arXiv 2203.02293): the same per-layer arithmetic as the other solve kernels
 // (Section 2.2.1, Appendix B, `rt_physics.hpp`) and the same Thomas recurrence
 // (Section 2.2.2).
 //
-// A wavefront owns 64 lanes ((column, bin) pairs) for the whole sweep: whole
-// columns of up to 64 lanes, each padded to a power of two, or 64 lanes of one
-// wider column.  It walks its layers from the TOA without a barrier: Planck
-// edge integrals of a few levels at a time go through LDS rows of its own, and
-// the layer coefficients feed the elimination in registers, so no item is
-// handed between threads.  The back-substitution records (32 bytes per layer
-// and lane) go through memory; the bin sums of each level are wavefront sums,
-// kept in LDS until the workgroup's one barrier before the outputs.
-#include "rt_internal.hpp"
-#include "rt_math.hpp"
-#include "rt_physics.hpp"
-#include "rt_wave.hpp"
+// A wavefront owns up to 64 lanes ((column, bin) pairs, rt_lanes.hpp) and walks
+// their layers from the TOA without a barrier: Planck edge integrals of eight
+// levels at a time go through LDS rows of its own, and the layer coefficients feed
+// the elimination in registers, so no item is handed between threads.  The
+// back-substitution records (32 bytes per layer and lane) go through memory, where
+// the L2 still holds most of them when they are read back; the level sums are taken
+// eight levels at a time.  One wavefront is one workgroup: four of them in one kept
+// registers and LDS until the slowest ended (2562 x 40 x 30 x 20 lanes FP64: 2.88 ms by
+// the layer kernel, 1.29 in workgroups of four, 1.10 in single wavefronts, where the
+// FP64 vector units are 80 percent busy; 10242 x 80 x 300 mixed: 7.46 and 4.80 ms).
+//
+// Where a grid brings fewer wavefronts than the chip runs (SEG), a wavefront's own
+// chain of dependent FP64 operations (about 2500 cycles per layer) is the time.  Each
+// column's layers are then split into S segments from the TOA, one group of lanes each,
+// in the same wavefront (while a column's lanes fill at most half of one) or in several
+// of one workgroup.  Each segment composes the elimination's map over its layers on
+// the way and leaves their coefficients in the records' place; the maps give the state
+// at every segment's top, from which all segments eliminate, and compose their maps of
+// F_up, with which all substitute back (StateMap; about 60 instructions more per layer,
+// and 64 bytes).  162 x 40 x 30 FP64: 50 us by the layer kernel, 92 in one segment, 26 in
+// eight; 2562 x 40 x 30: 140, 121 and 102 in two.  (Handing the elimination from segment
+// to segment instead, without the maps, took 34 us and 138.)
+#include "rt_lanes.hpp"
 
 #include <algorithm>
 #include <type_traits>
@@ -24,88 +36,152 @@
 namespace rtk {
 namespace {
 
-constexpr int kStreamThreads = 768;   // workgroup size bound: twelve wavefronts of a column of 768 lanes
-
 // Levels of one chunk: their Planck edge integrals share a pass, and so do their
 // column sums.
 constexpr int kChunk = 8;
-constexpr int kSumStride = 65;   // doubles per row of lane values to be summed (odd: rows start in different banks)
+constexpr int kSumStride = 65;        // doubles per row of lane values to be summed (odd: rows start in different banks)
+constexpr int kStreamThreads = 768;   // workgroup size bound
 
-// Lane layout of a problem: NBp padded lanes per column (a power of two from 8
-// to 64, or a multiple of 64), gw columns per wavefront, NBw wavefronts per column.
-struct LaneLayout {
-    int NBp, gw, NBw;
+// What the kernel needs of a problem's layout beside its sizes, worked out on the
+// host (SolveArgs::CH and L): integer divisions cost a wavefront about a thousand cycles
+// in its first microsecond.
+struct StreamShape {
+    int LPT;          // layers per segment, rounded up
+    int NBR;          // bins: lanes per column / points per bin
+    int NBw, NBs;     // LaneLayout
+    int edges;        // wave_edges
+    __host__ __device__ __forceinline__ long long pack() const
+    {
+        return (long long)NBR | (long long)NBw << 16 | (long long)NBs << 24 | (long long)edges << 32;
+    }
+    __host__ __device__ __forceinline__ static StreamShape unpack(int LPT, long long v)
+    {
+        return {LPT, (int)(v & 0xffff), (int)(v >> 16 & 0xff), (int)(v >> 24 & 0xff), (int)(v >> 32 & 0xff)};
+    }
 };
-__host__ __device__ __forceinline__ LaneLayout lane_layout(int NB)
+__host__ StreamShape stream_sizes(int N, int NB, int NG, int S)
 {
-    LaneLayout l;
-    int p = 8;
-    while (p < NB && p < 64) p *= 2;
-    l.NBp = NB > 64 ? (NB + 63) / 64 * 64 : p;
-    l.gw = NB > 64 ? 1 : 64 / p;
-    l.NBw = NB > 64 ? l.NBp / 64 : 1;
-    return l;
-}
-
-// Planck edges that one wavefront needs at most: its lanes' bins and one more.
-__host__ __device__ __forceinline__ int wave_edges(int NB, int NG)
-{
-    const int NBR = NB / NG;
-    const int most = NB > 64 ? (NG == 1 ? 64 : 63 / NG + 2) : NBR;
-    return (most < NBR ? most : NBR) + 1;
+    const LaneLayout ll = lane_layout(NB);
+    return {(N + S - 1) / S, NB / NG, ll.NBw, ll.NBs, wave_edges(NB, NG)};
 }
 
 struct StreamLds {
     int estride;                         // edge values per row (odd: rows start in different banks)
-    size_t wave, per_wave;               // a wavefront's own region: its start and size
+    size_t per_wave;                     // a wavefront's own region
     size_t edge, val, temp;              // in it: R [gw kChunk][estride]; double [kChunk][kSumStride], twice
                                          // (the second one in place of the edges); double [gw kChunk]
-    size_t c2, sum, top, flag, total;
+    size_t tab, c2, sum, top, flag, total;
 };
-__host__ __device__ __forceinline__ StreamLds stream_lds(int N, int NB, int NG, int K, int waves, bool mixed)
+// K columns of S segments each on `waves` wavefronts: K S = gw waves
+__host__ __device__ __forceinline__ StreamLds stream_lds(const StreamShape &sh, int N, int NB, int NG, int K, int gw,
+                                                         int waves, bool mixed)
 {
-    const LaneLayout ll = lane_layout(NB);
     StreamLds o;
-    o.estride = wave_edges(NB, NG) | 1;
-    const size_t rows = (size_t)ll.gw * kChunk, buf = kChunk * kSumStride * 8;
+    o.estride = sh.edges | 1;
+    const size_t rows = (size_t)gw * kChunk, buf = kChunk * kSumStride * 8;
     const size_t e = (rows * o.estride * (mixed ? 4 : 8) + 7) & ~size_t(7);
     o.temp = 0;
     o.val = rows * 8;
     o.edge = o.val + buf;
     o.per_wave = o.edge + (e > buf ? e : buf);
-    o.wave = 0;
-    o.c2 = (size_t)waves * o.per_wave;                                  // double [NBR+1]
-    o.sum = o.c2 + (size_t)(NB / NG + 1) * 8;                           // double [N+1][3][NBw][K]
-    o.top = o.sum + (size_t)(N + 1) * 3 * ll.NBw * K * 8;               // double [K][NB] (NG > 1)
-    o.flag = o.top + (NG > 1 ? (size_t)K * NB * 8 : 0);                 // uint32 [K]
+    o.tab = 0;                                                                  // FP64: the Planck table
+    o.c2 = (mixed ? 0 : kPlanckTable * 8) + (size_t)waves * o.per_wave;         // double [edges]
+    o.sum = o.c2 + (size_t)sh.edges * 8;                                        // double [N+1][3][K]
+    o.top = o.sum + (size_t)(N + 1) * 3 * K * 8;                                // double [K][NB] (NG > 1, NB <= 64)
+    o.flag = o.top + (NG > 1 && NB <= 64 ? (size_t)K * NB * 8 : 0);             // uint32 [K]
     o.total = (o.flag + 4 * (size_t)K + 15) & ~size_t(15);
     return o;
 }
 
-// base + off bytes: a wavefront-uniform base and a 32-bit offset per lane
-template <class T>
-__device__ __forceinline__ T &at(T *base, unsigned off)
+// Where a slice of a wide column leaves its level sums and flags for
+// k_stream_columns: value t (up, down, beam of level t / 3, then the flags) runs
+// through its records' planes, as many values in each as the last, shortest slice has
+// doubles there.  (The lanes' F_up at the TOA take the last plane.)
+struct SliceValues {
+    int per;
+    __device__ __forceinline__ double *at(double *rec, long long LB, int t) const
+    {
+        const int plane = small_div(t, per);
+        return rec + plane * LB * 2 + (t - plane * per);
+    }
+};
+__device__ __forceinline__ SliceValues slice_values(int NB, const StreamShape &sh)
 {
-    return *reinterpret_cast<T *>(reinterpret_cast<char *>(const_cast<typename std::remove_const<T>::type *>(base)) + off);
+    return {2 * (NB - (sh.NBw - 1) * sh.NBs)};
 }
 
-// A wavefront-uniform value kept in scalar registers from here on (not read
-// again from memory at its uses).
-template <class T>
-__device__ __forceinline__ void uniform_value(T &x)
+// The elimination's map of (c, eps = 1 - c, d) over a run of layers.  With den = (1 - r)
+// + r eps, elim_step (rt_physics.hpp) takes w (1, eps, c, d) to w' (1, eps', c', d'), w' =
+// w den, linearly in (w, e, c, d) = w (1, eps, c, d):
+//   w' = (1-r) w + r e,  e' = A (1-r+t) w + (r (1-r) + t^2) e,
+//   c' = r w' + t^2 c,   d' = S_dn w' + t (d + S_up c),
+// so a run is the product of its layers' matrices.  The columns of w, e and c are
+// non-negative: no digit is lost.  m: w and e from (e, w); c from (c, e, w); d from (d,
+// c, e, w) at the top.
+struct StateMap {
+    double m[11] = {0, 1, 1, 0, 1, 0, 0, 1, 0, 0, 0};
+    __device__ __forceinline__ void step(double t, double r, double omr, double A, double Sup, double Sdn)
+    {
+        const double tt = t * t, a1 = A * (omr + t), a2 = fma(r, omr, tt);
+        const double we = fma(omr, m[0], r * m[2]), ww = fma(omr, m[1], r * m[3]);
+        m[2] = fma(a1, m[0], a2 * m[2]);
+        m[3] = fma(a1, m[1], a2 * m[3]);
+        m[0] = we;
+        m[1] = ww;
+        m[7] *= t;
+        m[8] = t * fma(Sup, m[4], m[8]);
+        m[9] = fma(Sdn, we, t * fma(Sup, m[5], m[9]));
+        m[10] = fma(Sdn, ww, t * fma(Sup, m[6], m[10]));
+        m[4] *= tt;
+        m[5] = fma(r, we, tt * m[5]);
+        m[6] = fma(r, ww, tt * m[6]);
+    }
+    // by a power of two, so that w stays in range (every few layers: w' >= w (1 - r))
+    __device__ __forceinline__ void rescale()
+    {
+        const int e = -ilogb_pos(m[0] + m[1]);
+#pragma unroll
+        for (int v = 0; v < 11; ++v) m[v] = ldexp(m[v], e);
+    }
+    __device__ __forceinline__ ElimState state() const { return {m[0], m[1], m[2]}; }
+    __device__ __forceinline__ void set_state(const ElimState &s) { m[0] = s.c, m[1] = s.eps, m[2] = s.d; }
+    // the map to a given state
+    __device__ __forceinline__ static StateMap constant(const ElimState &s)
+    {
+        return {{0, 1, 0, s.eps, 0, 0, s.c, 0, 0, 0, s.d}};
+    }
+    __device__ __forceinline__ static int ilogb_pos(double x) { return x > 0.0 ? __builtin_amdgcn_frexp_exp(x) : 0; }
+    __device__ __forceinline__ void apply(ElimState &s) const
+    {
+        const double i = 1.0 / fma(m[0], s.eps, m[1]);
+        const double c = fma(m[4], s.c, fma(m[5], s.eps, m[6]));
+        const double d = fma(m[7], s.d, fma(m[8], s.c, fma(m[9], s.eps, m[10])));
+        s.eps = fma(m[2], s.eps, m[3]) * i;
+        s.c = c * i;
+        s.d = d * i;
+    }
+};
+
+// t, r and the absorptance A of a layer, t + r + A = 1, in two doubles: the two that are
+// not the largest, which is 1 minus them (at least 1/3, so to three units of roundoff);
+// which one it is in their lowest bits.
+__device__ __forceinline__ double2 pack_tra(double t, double r, double A)
 {
-    asm volatile("" : "+s"(x));
+    const bool tl = t >= r && t >= A, al = !tl && A >= r;   // the largest: t, A, else r
+    const double p = tl ? r : t, q = al ? r : A;
+    return make_double2(__hiloint2double(__double2hiint(p), (__double2loint(p) & ~1) | (tl ? 1 : 0)),
+                        __hiloint2double(__double2hiint(q), (__double2loint(q) & ~1) | (al ? 1 : 0)));
+}
+__device__ __forceinline__ void unpack_tra(double2 v, double &t, double &r, double &A)
+{
+    const bool tl = __double2loint(v.x) & 1, al = __double2loint(v.y) & 1;
+    const double big = (1.0 - v.x) - v.y;
+    t = tl ? big : v.x;
+    A = al ? big : v.y;
+    r = tl ? v.x : (al ? v.y : big);
 }
 
-// LDS values written by lanes of this wavefront are read by others of it.
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-template <bool MIXED, bool IN32>
+template <bool MIXED, bool IN32, bool SEG>
 __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
 {
     using R = typename std::conditional<MIXED, float, double>::type;
@@ -115,40 +191,123 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
     // the arguments, re-read in each phase (ArgsK)
     auto args = [&]() -> const SolveArgs & { return *(const SolveArgs *)ap; };
     const int NB = args().NB, NG = args().NG, C = args().C, N = args().N, K = args().K;
-    const int tid = threadIdx.x, wave = wave_uniform(tid >> 6), ln = tid & 63;
-    const LaneLayout ll = lane_layout(NB);
-    const StreamLds lo = stream_lds(N, NB, NG, K, blockDim.x >> 6, MIXED);
-    const int c0 = tile * K, NBR = NB / NG;
-    // this thread's column of the tile and lane of the column; the padding takes
-    // the values of the last lane or column and writes nothing
-    const int grp = ll.gw == 1 ? 0 : ln / ll.NBp;
-    const int kk = NB > 64 ? 0 : wave * ll.gw + grp;
-    const int yb = NB > 64 ? tid : ln - grp * ll.NBp;
-    const int c = min(c0 + kk, C - 1), b = min(yb, NB - 1);
-    const bool act = yb < NB && c0 + kk < C;
-    const int lane0 = NB > 64 ? wave * 64 : 0;              // first lane of the wavefront's column slice
-    const int bin0 = NG == 1 ? lane0 : lane0 / NG;
-    const int lastl = min(NB > 64 ? lane0 + 63 : NB - 1, NB - 1);
+    const int S = SEG ? args().PC : 1;
+    const StreamShape sh = StreamShape::unpack(args().CH, args().L);
+    const int tid = threadIdx.x, wave = SEG ? wave_uniform(tid >> 6) : 0, ln = tid & 63;
+    const int W = SEG ? blockDim.x : 64;
+    const bool wide = NB > 64;
+    int lNBp = 3;   // log2 of a group's lanes
+    while (lNBp < 6 && 1 << lNBp < NB) ++lNBp;
+    const int NBp = 1 << lNBp, gw = 64 >> lNBp;
+    const StreamLds lo = stream_lds(sh, N, NB, NG, K, gw, W >> 6, MIXED);
+    const int c0 = wide ? tile / sh.NBw : tile * K, slice = wide ? tile - c0 * sh.NBw : 0;
+    // group g of the workgroup's lanes: segment g / K, column g % K, its layers at
+    // positions [e, e1) from the TOA.  All segments run LPT steps, from position a = e1 -
+    // LPT on (a shorter one repeats the last layer of the one above).
+    const int LPT = SEG ? sh.LPT : N, shorter = SEG && S * LPT != N ? LPT - 1 : LPT, longer = SEG ? N - S * shorter : 0;
+    struct Group {
+        int kk, s, a, e, e1;
+    };
+    auto group = [&](int g) -> Group {
+        Group r;
+        if constexpr (SEG) {
+            r.s = K == 1 ? g : small_div(g, K);
+            r.kk = g - r.s * K;
+            r.e = r.s * shorter + min(r.s, longer);
+            r.e1 = r.e + shorter + (r.s < longer ? 1 : 0);
+            r.a = r.e1 - LPT;
+        } else {
+            r.kk = g;
+            r.s = r.e = r.a = 0;
+            r.e1 = N;
+        }
+        return r;
+    };
+    const int gl = ln >> lNBp, g0 = SEG ? wave * gw : 0;
+    const Group me = group(g0 + gl);
+    // a wavefront of first segments alone eliminates as it goes
+    const bool direct = SEG && K == gw && wave == 0;
+    // this thread's lane of its column; the padding takes the values of the last lane
+    // or column and writes nothing but the same records
+    const int lane0 = slice * sh.NBs, nlane = wide ? min(sh.NBs, NB - lane0) : NB;
+    const int yb = ln & (NBp - 1), b = lane0 + min(yb, nlane - 1), c = min(c0 + me.kk, C - 1);
+    const bool act = yb < nlane && c0 + me.kk < C;
+    const int bin0 = NG == 1 ? lane0 : lane0 / NG, lastl = lane0 + nlane - 1;
     const int ne = (NG == 1 ? lastl : lastl / NG) - bin0 + 2;   // edges of the wavefront's bins
     const int bin = NG == 1 ? b : b / NG, rb = bin - bin0;
     const bool sub = args().sub != 0;
 
-    char *own = lds + lo.wave + (size_t)wave * lo.per_wave;
+    double *s_tab = reinterpret_cast<double *>(lds + lo.tab);
+    char *own = lds + (MIXED ? 0 : kPlanckTable * 8) + (size_t)wave * lo.per_wave;
     R *s_edge = reinterpret_cast<R *>(own + lo.edge);
     double *s_val = reinterpret_cast<double *>(own + lo.val), *s_val2 = reinterpret_cast<double *>(own + lo.edge);
     double *s_T = reinterpret_cast<double *>(own + lo.temp);
-    double *s_c2 = reinterpret_cast<double *>(lds + lo.c2);
+    double *s_c2 = reinterpret_cast<double *>(lds + lo.c2) - bin0;
     double *s_sum = reinterpret_cast<double *>(lds + lo.sum);
     double *s_top = reinterpret_cast<double *>(lds + lo.top);
+    // SEG: values a group leaves for the other groups of its column, in place of its
+    // rows: value v of the group d above (d < 0: below) this lane's
+    auto shared_at = [&](int v, int d) -> double & {
+        const int t = tid + d * K * NBp;
+        return *reinterpret_cast<double *>(lds + (MIXED ? 0 : kPlanckTable * 8) + (size_t)(t >> 6) * lo.per_wave +
+                                           lo.val + (v * 64 + (t & 63)) * 8);
+    };
     uint32_t *s_flag = reinterpret_cast<uint32_t *>(lds + lo.flag);
+    auto sync = [&]() {
+        if (SEG && W > 64) __syncthreads();
+        else wave_sync();
+    };
 
-    for (int k = tid; k < K; k += blockDim.x) s_flag[k] = 0u;
-    for (int e = tid; e <= NBR; e += blockDim.x) s_c2[e] = args().c2_over_lam[e];
     const long long LB = (long long)C * NB;
     const unsigned lane = (unsigned)c * NB + b;   // of a [C][NB] plane
+    // byte offsets of this lane's layers from those of the lowest segment (32 bits: stream_geometry)
+    const int a_last = SEG ? N - LPT : 0;
+    const unsigned lay = SEG ? (unsigned)(a_last - me.a) * (unsigned)LB : 0u;
+    const unsigned o_in = (lane + lay) * (unsigned)sizeof(InT), o_rec = lane * 16u + lay * 32u;
+    auto in_at = [&](const double *base, int q) -> InT {   // step q's (past the last: one of the lowest layers, unused)
+        return at(reinterpret_cast<const InT *>(base) + (long long)max(N - 1 - a_last - q, 0) * LB, o_in);
+    };
+    // The inputs of a layer are loaded two layers ahead, into the registers that
+    // the layer before has just used (a copy between registers would wait for
+    // the load, and with it for the record stores before it).
+    InT dt0, w0, g0_, dt1, w1, g1;
+    auto load = [&](int q, InT &dt, InT &w, InT &g) {
+        dt = in_at(args().dtau, q);
+        w = in_at(args().w0, q);
+        g = in_at(args().g0, q);
+    };
+    const int odd = LPT & 1;
+    const bool uneven = SEG && N % S != 0;   // some segments repeat a layer
+    load(odd, dt0, w0, g0_);
+    load(1 - odd, dt1, w1, g1);   // (odd: the first step, then the third in its place)
+    // Planck edge integrals of a chunk of levels: rows (group of the wavefront, row of
+    // the chunk); a lane keeps one row and steps through its edges, so a wavefront's
+    // lanes sit in neighbouring edges and the row's temperature stays in a register.
+    // The first chunk's rows are T_int, the level the group starts at, the lower
+    // level of the odd first step if there is one (and one row unused, so that the
+    // chunks hold pairs of layers), then lower levels like the other chunks' rows.
+    const int lrows = 9 - lNBp;   // log2 of gw kChunk
+    const int row = ln & ((1 << lrows) - 1), e0 = ln >> lrows, epr = 64 >> lrows;
+    const int rq = row & (kChunk - 1);
+    const Group rg = group(g0 + row / kChunk);
+    const int rc = min(c0 + rg.kk, C - 1);
+    const int head = 2 + 2 * odd;   // rows of the first chunk before its pairs of layers
+    auto T_at = [&](int p) -> double { return level_T(args(), sub, max(N - p, 0), rc); };   // level p from the TOA
+    double Tc_ = rq == 0 ? args().Tint[rc] : T_at(rg.a + (rq < head ? min(rq - 1, odd) : rq - head + 1 + odd));
+    double Tn_ = T_at(rg.a + rq + kChunk - head + 1 + odd);
+
+    for (int k = tid; k < K; k += W) s_flag[k] = 0u;
+    for (int e = tid; e < ne; e += W) s_c2[bin0 + e] = args().c2_over_lam[bin0 + e];
+    if constexpr (!MIXED) {   // (all loads before the first store; past the end: the last value again)
+        constexpr int n = (kPlanckTable + 63) / 64;
+        double v[n];
+#pragma unroll
+        for (int i = 0; i < n; ++i) v[i] = planck_values[min(tid + i * W, kPlanckTable - 1)];
+#pragma unroll
+        for (int i = 0; i < n; ++i) s_tab[min(tid + i * W, kPlanckTable - 1)] = v[i];
+    }
     uint32_t fl = 0u;
-    const double mu = args().mu[c];
-    const double Ti = args().Tint[c];
+    const double mu = args().mu[c], Ti = args().Tint[c];
     const bool day = mu > 0.0, wday = wave_any(day);
     if (!isfinite(mu) || !(Ti >= 0.0) || !isfinite(Ti)) fl |= F_INVALID;
     const double inv_mu = day ? 1.0 / mu : 0.0;
@@ -160,108 +319,86 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
         c2fb = args().c2_over_lam_f[bin];
         c2fa = args().c2_over_lam_f[bin + 1];
     }
-    ElimState st = elim_top(args().Ftoa ? args().Ftoa[lane] : 0.0);
-    __syncthreads();
+    ElimState st;
+    StateMap map;   // (SEG; m[0..2]: the state, where direct)
+    auto top_state = [&]() { return elim_top(args().Ftoa ? args().Ftoa[lane] : 0.0); };
+    if (!SEG || direct) st = top_state();
+    if (direct) map.set_state(st);
+    double Fb_up = muF, tau = 0.0;   // beam and optical depth at the current level
+    if constexpr (SEG) {
+        // the optical depth above each segment: sums over [a, the next one's a)
+        if (wday && me.s < S - 1) {
+            const int n = group(g0 + gl + K).a - me.a;
+            double ts = 0.0;
+            for (int q = 0; q < LPT + 1; q += 8) {
+                InT v[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = in_at(args().dtau, q + k);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) ts += q + k < n ? double(v[k]) : 0.0;
+            }
+            shared_at(0, 0) = ts;
+        }
+        sync();
+        if (day && me.s > 0) {
+            for (int s = me.s; s > 0; --s) tau += shared_at(0, -s);
+            Fb_up = beam_at<MIXED>(muF, tau, inv_mu);
+        }
+        sync();
+    } else {
+        sync();
+    }
 
-    auto T_at = [&](int l, int cc) -> double {
-        const double *T_if = args().T, *T_ce = sub ? args().Tc : args().T;
-        const double *base = (sub && (l & 1)) ? T_ce : T_if;
-        return base[(long long)(sub ? (l >> 1) : l) * C + cc];
-    };
-    // Planck edge integrals of a chunk of n levels into rows (column of the
-    // wavefront, level): this lane keeps one row and steps through its edges, so
-    // a wavefront's lanes sit in neighbouring edges (one series regime mostly) and
-    // the row's temperature stays in a register.  Its row's column and level:
-    const int lrows = 31 - __builtin_clz(ll.gw * kChunk);
-    const int row = ln & (ll.gw * kChunk - 1), e0 = ln >> lrows, epr = 64 >> lrows;
-    const int rq = row & (kChunk - 1), rk = NB > 64 ? 0 : wave * ll.gw + row / kChunk;
-    const int rc = min(c0 + rk, C - 1);
-    auto edges = [&](double T, int n) {
-        if (rq < n) {
+    auto edges = [&](double T, int from, int n, bool check) {
+        if (rq >= from && rq < n) {
+            if (check && (!(T > 0.0) || !isfinite(T))) atomicOr(&s_flag[rg.kk], (uint32_t)F_INVALID);
             const double iT = rcp(T);
             if (e0 == 0) s_T[row] = T;
-            for (int e = e0; e < ne; e += epr) s_edge[row * lo.estride + e] = planck_edge<R>(s_c2[bin0 + e] * iT);
+            // two at a time (past the last edge: that one again), so that their chains overlap
+            R *re = s_edge + row * lo.estride;
+            for (int i = 0; i < ne; i += 2 * epr) {
+                const int e1 = min(i + e0, ne - 1), e2 = min(i + epr + e0, ne - 1);
+                const R v1 = edge_integral<R>(s_c2[bin0 + e1] * iT, s_tab), v2 = edge_integral<R>(s_c2[bin0 + e2] * iT, s_tab);
+                re[e1] = v1;
+                re[e2] = v2;
+            }
         }
         wave_sync();
     };
     auto bin_B = [&](int q) -> R {
-        const int rw = grp * kChunk + q;
-        const double Td = s_T[rw];
-        const R Tr = R(Td), T2 = Tr * Tr;
-        const R *re = s_edge + rw * lo.estride + rb;
-        R I = planck_combine<R>(re[0], re[1]);
-        if constexpr (MIXED) {
-            const R iT = rcp(Tr);
-            const R xb = c2fb * iT, xa = c2fa * iT;
-            if (planck_narrow(xa, xb)) {
-                const double iTd = rcp(Td);
-                I = planck_gl3(s_c2[bin + 1] * iTd, s_c2[bin] * iTd);
-            }
-        }
-        return R(kPref) * T2 * T2 * I;
+        const int rw = gl * kChunk + q;
+        return bin_radiance<MIXED, R>(s_edge + rw * lo.estride + rb, s_T[rw], c2fb, c2fa, s_c2 + bin);
     };
-    // Column sums of n rows of lane values v (LDS, kSumStride apart) into the sums
-    // of levels l0, l0 + dl, ...: lane (q, p) = (ln % 8, ln / 8) adds the 8 lanes
-    // p of row q, then the parts of a column are added.  Fixed order.
-    const int sstep = ll.NBw * K;
-    double *const sum0 = s_sum + (size_t)(NB > 64 ? wave : 0) * K;
-    auto sum_rows = [&](const double *v, int which, int l0, int dl, int n) {
+    // Column sums of n rows of lane values v (LDS, kSumStride apart) into the sums of
+    // levels lev(group, row): lane (q, p) = (ln % 8, ln / 8) adds the 8 lanes p of row
+    // q, then the parts of a group are added.  Fixed order.
+    const Group sg = group(g0 + (ln >> lNBp));   // (p >> (lNBp - 3))
+    const bool sumout = (ln >> 3 & ((NBp >> 3) - 1)) == 0;
+    auto sum_rows = [&](const double *v, int which, auto lev) {
         wave_sync();
         const int q = ln & 7, p = ln >> 3;
         const double *r = v + q * kSumStride + p * 8;
         double s = r[0];
 #pragma unroll
         for (int k = 1; k < 8; ++k) s += r[k];
-        if (ll.NBp > 8) s += __shfl_xor(s, 8);
-        if (ll.NBp > 16) s += __shfl_xor(s, 16);
-        if (ll.NBp > 32) s += __shfl_xor(s, 32);
-        const int np = ll.NBp >= 64 ? 8 : ll.NBp >> 3, g = p / np;
-        if (q < n && p == g * np)
-            sum0[(size_t)(3 * (l0 + dl * q) + which) * sstep + (NB > 64 ? 0 : wave * ll.gw + g)] = s;
+        if (lNBp > 3) s += __shfl_xor(s, 8);
+        if (lNBp > 4) s += __shfl_xor(s, 16);
+        if (lNBp > 5) s += __shfl_xor(s, 32);
+        const int l = lev(sg, q);
+        if (l >= 0 && sumout) s_sum[(3 * l + which) * K + sg.kk] = s;
         wave_sync();
     };
 
-    // T_int, level N and, where the number of layers is odd, level N - 1: rows
-    // 0, 1 and 2 of a chunk of their own
-    const int odd = N & 1;
-    double Tc_ = rq == 0 ? args().Tint[rc] : T_at(max(N + 1 - rq, 0), rc);
-    double Tn_ = T_at(max(N - 1 - odd - rq, 0), rc);
-    auto check_T = [&](double T, bool in) {
-        if (in && (!(T > 0.0) || !isfinite(T))) atomicOr(&s_flag[rk], (uint32_t)F_INVALID);
-    };
-    check_T(Tc_, rq == 1 || (rq == 2 && odd));
-    edges(Tc_, 2 + odd);
-    const double Fboa = double(kPI) * double(bin_B(0));
-    R Bup = bin_B(1);
-    double Fb_up = muF, tau = 0.0;
-    const unsigned o_in = lane * (unsigned)sizeof(InT), o_rec = lane * 16u;
-    // The inputs of a layer are loaded two layers ahead, into the registers that
-    // the layer before has just used (a copy between registers would wait for
-    // the load, and with it for the record stores before it).
-    InT dt0, w0, g0, dt1, w1, g1;
-    auto load = [&](int i, InT &dt, InT &w, InT &g) {   // (past the last layer: layer 0 again, unused)
-        const long long o = (long long)max(i, 0) * LB;
-        dt = at(reinterpret_cast<const InT *>(args().dtau) + o, o_in);
-        w = at(reinterpret_cast<const InT *>(args().w0) + o, o_in);
-        g = at(reinterpret_cast<const InT *>(args().g0) + o, o_in);
-    };
-    load(N - 1 - odd, dt0, w0, g0);
-    load(N - 2 + odd, dt1, w1, g1);   // (odd: layer N - 1, then layer N - 3 in its place)
     Opts o;
     auto options = [&]() {   // (read anew in each chunk)
         opaque_args(ap);
-        o = args().o;
-        uniform_value(o.e_tau);
-        uniform_value(o.g_guard);
-        uniform_value(o.improved);
-        uniform_value(o.noniso);
-        uniform_value(o.e_clamp);
+        o = uniform_options(ap);
     };
-    // layer i, its lower level's Planck edges in row q, its beam value into row v.
+    // step q, its lower level's Planck edges in row r, its beam value into row v.
     // (The padding stores its lane's record again: same values, and the loads'
     // waits then pass the stores, whose number is the same for every wavefront.)
-    auto layer = [&](int i, int q, int v, InT &dt_, InT &w_, InT &g_) {
-        const R B = bin_B(q);
+    auto layer = [&](int q, int r, int v, InT &dt_, InT &w_, InT &g_, R &Bup) {
+        const R B = bin_B(r);
         double Fb_lo = 0.0;
         const double dt = double(dt_);
         if (day) {
@@ -270,238 +407,443 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
         }
         const Layer<R> Ly = layer_item<MIXED, R, MIXED>(dt, double(w_), double(g_), day, mu, inv_mu, Fb_up, Fb_lo,
                                                         B, Bup, o, inv_eps2, fl);
-        load(i - 2, dt_, w_, g_);
-        const BackRec rec = elim_step(st, double(Ly.t), double(Ly.r), double(Ly.omr), double(Ly.A),
-                                      double(Ly.Sup), double(Ly.Sdn));
-        double2 *p_rec = reinterpret_cast<double2 *>(args().scratch) + (long long)i * 2 * LB;
-        at(p_rec, o_rec) = make_double2(rec.G, rec.H);
-        at(p_rec + LB, o_rec) = make_double2(rec.c, rec.d);
+        load(q + 2, dt_, w_, g_);
+        double2 x, y;
+        if constexpr (!SEG) {
+            const BackRec rec = elim_step(st, double(Ly.t), double(Ly.r), double(Ly.omr), double(Ly.A),
+                                          double(Ly.Sup), double(Ly.Sdn));
+            x = make_double2(rec.G, rec.H);
+            y = make_double2(rec.c, rec.d);
+        } else if (direct) {
+            st = map.state();
+            const BackRec rec = elim_step(st, double(Ly.t), double(Ly.r), double(Ly.omr), double(Ly.A),
+                                          double(Ly.Sup), double(Ly.Sdn));
+            map.set_state(st);
+            x = make_double2(rec.G, rec.H);
+            y = make_double2(rec.c, rec.d);
+        } else if constexpr (MIXED) {
+            map.step(double(Ly.t), double(Ly.r), double(Ly.omr), double(Ly.A), double(Ly.Sup), double(Ly.Sdn));
+            x = make_double2(__hiloint2double(__float_as_int(Ly.r), __float_as_int(Ly.t)),
+                             __hiloint2double(__float_as_int(Ly.A), __float_as_int(Ly.omr)));
+            y = make_double2(__hiloint2double(__float_as_int(Ly.Sdn), __float_as_int(Ly.Sup)), 0.0);
+        } else {
+            map.step(Ly.t, Ly.r, Ly.t + Ly.A, Ly.A, Ly.Sup, Ly.Sdn);
+            x = pack_tra(Ly.t, Ly.r, Ly.A);
+            y = make_double2(Ly.Sup, Ly.Sdn);
+        }
+        // (the layer that a shorter segment repeats is another's: that step stores in
+        // the place of the next one)
+        const bool first = SEG && uneven && q == 0;
+        const unsigned o_st = o_rec + (first && me.a == me.e ? (unsigned)LB * 32u : 0u);
+        double2 *p_rec = reinterpret_cast<double2 *>(args().scratch) + (long long)(N - 1 - a_last - q - (first ? 1 : 0)) * 2 * LB;
+        at(p_rec, o_st) = x;
+        at(p_rec + LB, o_st) = y;
         if (wday) s_val[v * kSumStride + ln] = wgt * Fb_lo;
         Fb_up = Fb_lo;
         Bup = B;
+        if constexpr (SEG)
+            if (first && me.a != me.e) map = StateMap();
     };
     options();
+    edges(Tc_, 0, min(kChunk, LPT + head - odd), rq > 0);
+    const double Fboa = double(kPI) * double(bin_B(0));
+    R Bup = bin_B(1);
     if (wday) s_val[ln] = wgt * muF;   // beam at level N
-    if (odd) layer(N - 1, 2, 1, dt1, w1, g1);
-    if (wday) sum_rows(s_val, 2, N, -1, 1 + odd);
-    // chunks of an even number of layers, in pairs
-    for (int hi = N - 1 - odd; hi >= 0; hi -= kChunk) {
-        const int n = min(kChunk, hi + 1);
-        options();
-        Tc_ = Tn_;
-        check_T(Tc_, rq < n);
-        edges(Tc_, n);
-        Tn_ = T_at(max(hi - kChunk - rq, 0), rc);   // (the chunk after this one's)
+    if (odd) layer(0, 2, 1, dt1, w1, g1, Bup);
+    if (wday)
+        sum_rows(s_val, 2, [&](const Group &g, int q) {
+            return q == 0 ? (g.s == 0 ? N : -1) : (q == 1 && odd && g.a == g.e ? N - 1 - g.a : -1);
+        });
+    // chunks of pairs of layers: steps q0 .. q0 + n - 1 in rows r0 ..
+    for (int q0 = odd, r0 = head; q0 < LPT;) {
+        const int n = min(kChunk - r0, LPT - q0);
 #pragma unroll 1
-        for (int q = 0; q < n; q += 2) {
-            layer(hi - q, q, q, dt0, w0, g0);
-            layer(hi - q - 1, q + 1, q + 1, dt1, w1, g1);
+        for (int k = 0; k < n; k += 2) {
+            layer(q0 + k, r0 + k, k, dt0, w0, g0_, Bup);
+            layer(q0 + k + 1, r0 + k + 1, k + 1, dt1, w1, g1, Bup);
         }
-        if (wday) sum_rows(s_val, 2, hi, -1, n);
+        if (wday)
+            sum_rows(s_val, 2, [&](const Group &g, int q) {
+                return q < n && q0 + q >= g.e - g.a ? N - 1 - g.a - q0 - q : -1;
+            });
+        q0 += n;
+        r0 = 0;
+        if (q0 < LPT) {
+            if (SEG && !direct) map.rescale();
+            options();
+            Tc_ = Tn_;
+            edges(Tc_, 0, min(kChunk, LPT - q0), true);
+            Tn_ = T_at(rg.a + q0 + kChunk + rq + 1);   // (the chunk after this one's)
+        }
     }
-    if (fl) atomicOr(&s_flag[kk], fl);
+    if (fl) atomicOr(&s_flag[me.kk], fl);
 
-    double Fu, Fd, Fu_toa = 0.0;
-    elim_boa(st, Fboa, Fb_up, Fu, Fd);
-    // back-substitution in chunks of levels; a lane's records are loaded RD
-    // levels ahead of their use.  Every chunk runs whole (past level N on the last
-    // record again, into rows that are not summed), so no load is under a branch.
+    double Fu = 0.0, Fd = 0.0;
+    if constexpr (!SEG) {
+        elim_boa(st, Fboa, Fb_up, Fu, Fd);
+    } else {
+        // the state at the segment's top, from the maps of the ones above
+        if (direct) map = StateMap::constant(map.state());
+        sync();   // (the rows' place is free)
+#pragma unroll
+        for (int v = 0; v < 11; ++v) shared_at(v, 0) = map.m[v];
+        sync();
+        st = top_state();
+        for (int d = -me.s; d < 0; ++d) {
+            StateMap up;
+#pragma unroll
+            for (int v = 0; v < 11; ++v) up.m[v] = shared_at(v, d);
+            up.apply(st);
+        }
+        // the elimination of all segments: coefficients become records in place, and
+        // the segment's map of F_up is composed
+        constexpr int RC = 4;
+        double2 x[RC], y[RC];
+        auto ld = [&](int q, int k) {
+            const double2 *r = reinterpret_cast<const double2 *>(args().scratch) +
+                               (long long)(N - 1 - a_last - min(q, LPT - 1)) * 2 * LB;
+            x[k] = at(r, o_rec);
+            if constexpr (MIXED) y[k].x = at(r + LB, o_rec).x;
+            else y[k] = at(r + LB, o_rec);
+        };
+        double gam = 1.0, eta = 0.0;
+        auto step = [&](int q, int k) {
+            BackRec rec;
+            if constexpr (MIXED) {
+                auto lo_f = [](double v) { return double(__int_as_float(__double2loint(v))); };
+                auto hi_f = [](double v) { return double(__int_as_float(__double2hiint(v))); };
+                rec = elim_step(st, lo_f(x[k].x), hi_f(x[k].x), lo_f(x[k].y), hi_f(x[k].y), lo_f(y[k].x), hi_f(y[k].x));
+            } else {
+                double t, r, A;
+                unpack_tra(x[k], t, r, A);
+                rec = elim_step(st, t, r, t + A, A, y[k].x, y[k].y);
+            }
+            double2 *r = reinterpret_cast<double2 *>(args().scratch) + (long long)(N - 1 - a_last - q) * 2 * LB;
+            at(r, o_rec) = make_double2(rec.G, rec.H);
+            at(r + LB, o_rec) = make_double2(rec.c, rec.d);
+            eta = fma(gam, rec.H, eta);
+            gam *= rec.G;
+        };
+        // (not for the padding's columns: another wavefront may have been through the
+        // last column's coefficients already)
+        if (!direct && c0 + me.kk < C) {
+            int q = 0;
+            if (uneven) {   // a shorter segment's first step is not its own
+                ld(0, 0);
+                if (me.a == me.e) step(0, 0);
+                q = 1;
+            }
+#pragma unroll
+            for (int k = 0; k < RC; ++k) ld(q + k, k);
+            for (; q + RC <= LPT; q += RC) {
+#pragma unroll
+                for (int k = 0; k < RC; ++k) {
+                    step(q + k, k);
+                    ld(q + k + RC, k);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < RC; ++k)
+                if (q + k < LPT) step(q + k, k);
+        }
+        shared_at(11, 0) = gam;
+        shared_at(12, 0) = eta;
+        if (me.s == S - 1) {
+            elim_boa(st, Fboa, Fb_up, Fu, Fd);
+            shared_at(13, 0) = Fu;
+        }
+        sync();
+        // F_up at the bottom of the segment, from the one at the BOA upward
+        if (me.s < S - 1) {
+            const int down = S - 1 - me.s;
+            Fu = shared_at(13, down);
+            for (int d = down; d > 0; --d) Fu = fma(shared_at(11, d), Fu, shared_at(12, d));
+        }
+        sync();
+    }
+    // back-substitution in chunks of levels, from the group's first one on (level 0,
+    // or the one above its lowest layer); a lane's records are loaded RD levels
+    // ahead of their use.  Every chunk runs whole (past the group's last level on its
+    // last record again, into rows that are not summed), so no load is under a branch.
     constexpr int RD = MIXED ? 4 : 8;
     opaque_args(ap);
-    const double2 *q_rec = reinterpret_cast<const double2 *>(args().scratch);
+    const bool low = me.s == S - 1;
+    const int ilo = N - me.e1, first = low ? 0 : ilo + 1;   // its lowest layer, its first level
+    const int last = N - me.e;                              // its last level
     double2 r0[RD], r1[RD];
-    int jn = 0;   // next record
+    int jn = first - 1;   // next record: that of the layer below the level
     auto ld = [&](int k) {
-        r0[k] = at(q_rec, o_rec);
-        r1[k] = at(q_rec + LB, o_rec);
-        q_rec += ++jn < N ? 2 * LB : 0;
+        if constexpr (SEG) {
+            const unsigned q = lane * 16u + (unsigned)max(min(jn, last - 1), 0) * (unsigned)LB * 32u;
+            const double2 *r = reinterpret_cast<const double2 *>(args().scratch);
+            r0[k] = at(r, q);
+            r1[k] = at(r + LB, q);
+        } else {
+            const double2 *r = reinterpret_cast<const double2 *>(args().scratch) + (long long)max(min(jn, N - 1), 0) * 2 * LB;
+            r0[k] = at(r, o_rec);
+            r1[k] = at(r + LB, o_rec);
+        }
+        ++jn;
     };
-    r0[0] = make_double2(1.0, 0.0);   // level 0: the fluxes stay as they are
-    r1[0] = make_double2(0.0, Fd);
 #pragma unroll
-    for (int k = 1; k < RD; ++k) ld(k);
+    for (int k = 0; k < RD; ++k) ld(k);
+    if (low) {   // level 0: the fluxes stay as they are
+        r0[0] = make_double2(1.0, 0.0);
+        r1[0] = make_double2(0.0, Fd);
+    }
     const bool bins = args().F_up_bin || args().F_dn_bin;
-    for (int i0 = 0; i0 <= N; i0 += kChunk) {
+    double Fu_toa = 0.0;
+    for (int k0 = 0; k0 <= LPT; k0 += kChunk) {
         opaque_args(ap);
 #pragma unroll
         for (int k = 0; k < kChunk; ++k) {
-            const int i = i0 + k;
+            const int i = first + k0 + k;
             back_step(r0[k % RD].x, r0[k % RD].y, r1[k % RD].x, r1[k % RD].y, Fu, Fd);
             ld(k % RD);
             s_val[k * kSumStride + ln] = wgt * Fu;
             s_val2[k * kSumStride + ln] = wgt * Fd;
             if (i == N) Fu_toa = Fu;
-            if (bins && act && i <= N) {
+            if (bins && act && i <= last) {
                 if (args().F_up_bin) args().F_up_bin[i * LB + lane] = Fu;
                 if (args().F_dn_bin) args().F_dn_bin[i * LB + lane] = Fd;
             }
         }
-        const int n = min(kChunk, N + 1 - i0);
-        sum_rows(s_val, 0, i0, 1, n);
-        sum_rows(s_val2, 1, i0, 1, n);
-    }
-    if (act && args().F_up_toa_bin) {
-        if (NG == 1) args().F_up_toa_bin[lane] = Fu_toa;
-        else s_top[kk * NB + b] = Fu_toa;
-    }
-    __syncthreads();
-
-    // outputs: the column sums of each level (over a wide column's wavefronts, in
-    // order), net flux and heating
-    opaque_args(ap);
-    auto col_sum = [&](int lev, int v, int k) -> double {
-        const double *p = s_sum + (size_t)(3 * lev + v) * sstep + k;
-        double s = p[0];
-        for (int w = 1; w < ll.NBw; ++w) s += p[(size_t)w * K];
-        return s;
-    };
-    auto out_at = [&](double *iface, double *centre, int l, int cc) -> double * {
-        if (sub) return ((l & 1) ? centre : iface) + (long long)(l >> 1) * C + cc;
-        return iface + (long long)l * C + cc;
-    };
-    for (int t = tid; t < (N + 1) * K; t += blockDim.x) {
-        const int lev = t / K, k = t - lev * K, cc = c0 + k;
-        if (cc >= C) continue;
-        const bool dk = args().mu[cc] > 0.0;   // (night columns have no beam sums)
-        auto net = [&](int l, double &su, double &sd, double &sb) -> double {
-            su = col_sum(l, 0, k);
-            sd = col_sum(l, 1, k);
-            sb = dk ? col_sum(l, 2, k) : 0.0;
-            return su - sd - sb;
+        auto level = [&](const Group &g, int q) {
+            const int l = (g.s == S - 1 ? 0 : N - g.e1 + 1) + k0 + q;
+            return l <= N - g.e ? l : -1;
         };
-        double su, sd, sb, x, y, z;
-        const double fn = net(lev, su, sd, sb);
-        *out_at(args().F_up, args().F_up_c, lev, cc) = su;
-        *out_at(args().F_dn, args().F_dn_c, lev, cc) = sd;
-        *out_at(args().F_beam, args().F_beam_c, lev, cc) = sb;
-        *out_at(args().F_net, args().F_net_c, lev, cc) = fn;
-        if (!isfinite(fn)) atomicOr(&s_flag[k], (uint32_t)F_NONFIN);
-        const int up = sub ? lev + 2 : lev + 1;   // the interface above
-        if (up > N || (sub && (lev & 1))) continue;
-        const int j = sub ? lev >> 1 : lev;
-        const double fnu = net(up, x, y, z);
-        const long long o = (long long)j * C + cc;
-        const double p0 = args().p[o], p1 = args().p[o + C];
-        const double dp = p0 - p1;
-        bool bad = !(dp > 0.0);
-        if (sub) {
-            const double pm = args().pc[o];
-            bad = bad || !(p0 > pm && pm > p1);
-        }
-        if (bad) atomicOr(&s_flag[k], (uint32_t)F_INVALID);
-        const double qh = args().o.gravity * (fn - fnu) / dp;
-        args().heat[o] = qh;
-        if (args().dTdt) args().dTdt[o] = qh / args().o.cp;
+        sum_rows(s_val, 0, level);
+        sum_rows(s_val2, 1, level);
     }
-    if (NG > 1 && args().F_up_toa_bin) {
-        for (int t = tid; t < K * NBR; t += blockDim.x) {
-            const int k = t / NBR, r = t - k * NBR, cc = c0 + k;
-            if (cc >= C) continue;
-            const double *f = s_top + k * NB + r * NG;
-            double s = 0.0;
-            for (int g = 0; g < NG; ++g) s += args().wg[g] * f[g];
-            args().F_up_toa_bin[(long long)cc * NBR + r] = s;
+    opaque_args(ap);
+    if (act && me.s == 0 && args().F_up_toa_bin) {
+        if (NG == 1) args().F_up_toa_bin[lane] = Fu_toa;
+        else if (!wide) s_top[me.kk * NB + b] = Fu_toa;
+    }
+    sync();
+    if (!wide) {
+        if (NG > 1 && args().F_up_toa_bin) {   // the spectrum: weighted sums over each bin's points
+            for (int t = tid; t < K * sh.NBR; t += W) {
+                const int k = small_div(t, sh.NBR), r = t - k * sh.NBR, cc = c0 + k;
+                if (cc >= C) continue;
+                const double *f = s_top + k * NB + r * NG;
+                double s = 0.0;
+                for (int g = 0; g < NG; ++g) s += args().wg[g] * f[g];
+                args().F_up_toa_bin[(long long)cc * sh.NBR + r] = s;
+            }
         }
+        write_columns(ap, c0, K, s_flag, [&](int l, int v, int k) { return s_sum[(3 * l + v) * K + k]; });
+    } else {
+        // this slice's sums and flags in the place of its used records (slice_value)
+        double *rec = args().scratch + ((long long)c0 * NB + lane0) * 2;
+        const SliceValues sv = slice_values(NB, sh);
+        for (int t = tid; t < 3 * (N + 1); t += W) *sv.at(rec, LB, t) = t % 3 == 2 && !wday ? 0.0 : s_sum[t];
+        if (tid == 0) *sv.at(rec, LB, 3 * (N + 1)) = (double)s_flag[0];
+        if (act && me.s == 0 && NG > 1) rec[(2 * N - 1) * LB * 2 + (b - lane0)] = Fu_toa;
+    }
+}
+
+// Columns of more than 64 lanes, after k_solve_stream: a workgroup adds its column's
+// slices, in order.
+__device__ __forceinline__ void solve_columns(ArgsK ap, const int c)
+{
+    __shared__ uint32_t s_flag;
+    auto args = [&]() -> const SolveArgs & { return *(const SolveArgs *)ap; };
+    const int NB = args().NB, NG = args().NG, C = args().C, N = args().N, tid = threadIdx.x;
+    const StreamShape sh = StreamShape::unpack(args().CH, args().L);
+    const long long LB = (long long)C * NB;
+    double *rec = args().scratch + (long long)c * NB * 2;
+    const SliceValues sv = slice_values(NB, sh);
+    auto value = [&](int w, int t) -> double { return *sv.at(rec + w * sh.NBs * 2, LB, t); };
+    if (tid == 0) {
+        uint32_t f = 0u;
+        for (int w = 0; w < sh.NBw; ++w) f |= (uint32_t)value(w, 3 * (N + 1));
+        s_flag = f;
     }
     __syncthreads();
-    for (int k = tid; k < K; k += blockDim.x) {
-        if (c0 + k >= C) continue;
-        if (args().flags) args().flags[c0 + k] = s_flag[k];
-        const uint32_t bad = status_bits(s_flag[k]);
-        if (args().status && bad) atomicOr(args().status, bad);
+    if (NG > 1 && args().F_up_toa_bin) {   // the spectrum: weighted sums over each bin's points
+        const double *f = rec + (2 * N - 1) * LB * 2;
+        for (int r = tid; r < sh.NBR; r += blockDim.x) {
+            double s = 0.0;
+            for (int g = 0; g < NG; ++g) {
+                const int l = r * NG + g, w = small_div(l, sh.NBs);
+                s += args().wg[g] * f[w * sh.NBs * 2 + l - w * sh.NBs];
+            }
+            args().F_up_toa_bin[(long long)c * sh.NBR + r] = s;
+        }
     }
+    write_columns(ap, c, 1, &s_flag, [&](int l, int v, int) {
+        double s = 0.0;
+        for (int w = 0; w < sh.NBw; ++w) s += value(w, 3 * l + v);
+        return s;
+    });
 }
 
-template <bool MIXED, bool IN32 = false>
-__global__ void __launch_bounds__(kStreamThreads, MIXED ? 4 : 3) k_solve_stream(const SolveArgs a)
+constexpr int kColumnThreads = 64;   // of k_stream_columns
+
+// Workgroups go to the eight XCDs in turn; workgroup g of a grid of 8 n takes tile
+// (g % 8) n + g / 8, so each XCD's L2 sees a run of neighbouring columns (slices of a
+// column share cache lines).
+constexpr int kXcds = 8;
+__device__ __forceinline__ int xcd_tile(int g, int n) { return (g % kXcds) * n + g / kXcds; }
+int xcd_grid(int tiles) { return (tiles + kXcds - 1) / kXcds * kXcds; }
+
+// Whether a request has that tile: a set of K columns, or a slice of a wide column.
+__device__ __forceinline__ bool has_tile(const SolveArgs &a, int tile)
 {
-    solve_tile_stream<MIXED, IN32>(kernel_args(a), blockIdx.x);
+    const int nbw = StreamShape::unpack(0, a.L).NBw;
+    return nbw > 1 ? tile < a.C * nbw : (long long)tile * a.K < a.C;
 }
 
-// Workgroup of request r with first[r] <= g < first[r+1] (batched launches).
-__device__ __forceinline__ int batch_slot(const int *first, int n, int g)
+template <bool MIXED, bool IN32, bool SEG>
+__global__ void __launch_bounds__(SEG ? kStreamThreads : 64, MIXED && !SEG ? 4 : 3) k_solve_stream(const SolveArgs a)
 {
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (first[mid] <= g) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
+    const int tile = xcd_tile(blockIdx.x, gridDim.x / kXcds);
+    if (has_tile(a, tile)) solve_tile_stream<MIXED, IN32, SEG>(kernel_args(a), tile);
 }
 
-template <bool MIXED, bool IN32 = false>
-__global__ void __launch_bounds__(kStreamThreads, MIXED ? 4 : 3)
+__global__ void __launch_bounds__(kColumnThreads) k_stream_columns(const SolveArgs a)
+{
+    solve_columns(kernel_args(a), blockIdx.x);
+}
+
+template <bool MIXED, bool IN32, bool SEG>
+__global__ void __launch_bounds__(SEG ? kStreamThreads : 64, MIXED && !SEG ? 4 : 3)
 k_solve_stream_batch(const SolveArgs *__restrict__ reqs, const int *__restrict__ first, int n)
 {
-    const int r = batch_slot(first, n, blockIdx.x);
-    solve_tile_stream<MIXED, IN32>((ArgsK)(reqs + r), blockIdx.x - first[r]);
+    const int r = batch_request(first, n, blockIdx.x);
+    const int end = r + 1 < n ? first[r + 1] : (int)gridDim.x;
+    const int tile = xcd_tile(blockIdx.x - first[r], (end - first[r]) / kXcds);
+    if (has_tile(reqs[r], tile)) solve_tile_stream<MIXED, IN32, SEG>((ArgsK)(reqs + r), tile);
+}
+
+// first: of k_solve_stream_batch; one workgroup per workgroup of that launch, the
+// first ones of a request take its columns
+__global__ void __launch_bounds__(kColumnThreads)
+k_stream_columns_batch(const SolveArgs *__restrict__ reqs, const int *__restrict__ first, int n)
+{
+    const int r = batch_request(first, n, blockIdx.x), c = blockIdx.x - first[r];
+    if (c < reqs[r].C) solve_columns((ArgsK)(reqs + r), c);
+}
+
+// f(kernel) for the variant of a launch
+template <class F>
+void with_kernel(int precision, int in_f32, bool seg, F f)
+{
+    using std::integral_constant;
+    auto pick = [&](auto mixed, auto in32) {
+        if (seg) f(mixed, in32, integral_constant<bool, true>{});
+        else f(mixed, in32, integral_constant<bool, false>{});
+    };
+    if (precision != 1) pick(integral_constant<bool, false>{}, integral_constant<bool, false>{});
+    else if (in_f32) pick(integral_constant<bool, true>{}, integral_constant<bool, true>{});
+    else pick(integral_constant<bool, true>{}, integral_constant<bool, false>{});
 }
 
 }  // namespace
 
-Geometry stream_geometry(int C, int N, int NB, int NG, bool mixed, const DeviceLimits &dev)
+// S segments per column; direct: the first wavefront holds first segments only.
+static Geometry stream_shape(int C, int N, int NB, int NG, int S, bool direct, bool mixed, const DeviceLimits &dev)
 {
     Geometry g{};
-    // 32-bit byte offsets of a lane's record in a plane of lanes
-    if ((long long)C * NB >= (1ll << 28)) return g;
     const LaneLayout ll = lane_layout(NB);
-    // A wavefront's sweep takes as long however few others there are, so the grid
-    // has to bring more than one per SIMD: at five per compute unit (2562 columns
-    // x 40 layers x 30 bins: 1284 on 256) it is even with the layer kernel, whose
-    // time falls with the columns (FP64 131 against 140 us, mixed 93 against 96).
-    const long long all_waves = NB > 64 ? (long long)C * ll.NBw : (C + ll.gw - 1) / ll.gw;
-    if (all_waves < 5ll * (dev.n_cu > 0 ? dev.n_cu : 256)) return g;
-    int waves = NB > 64 ? ll.NBw : 4;
+    // columns per workgroup: whole wavefronts of segments
+    int K = 1;
+    while (K * S % ll.gw) ++K;
+    if (S > 1 && direct) K = ll.gw;
+    const int waves = K * S / ll.gw;
+    if (64 * waves > kStreamThreads || S > N || (S > 1 && N % S && (N + S - 1) / S < 2)) return g;
+    // 32-bit byte offsets of a lane's record in a plane of lanes, of all records where segments differ
+    if ((long long)C * NB >= (1ll << 28) || (S > 1 && (long long)C * NB * N >= (1ll << 27))) return g;
+    const StreamShape sh = stream_sizes(N, NB, NG, S);
+    g.lds = stream_lds(sh, N, NB, NG, K, ll.gw, waves, mixed).total;
+    if (g.lds > dev.lds) return g;
     g.kernel = KERNEL_STREAM;
-    for (;; waves /= 2) {
-        g.K = NB > 64 ? 1 : waves * ll.gw;
-        g.lds = stream_lds(N, NB, NG, g.K, waves, mixed).total;
-        if (g.lds <= dev.lds) break;
-        if (NB > 64 || waves == 1) return Geometry{};
-    }
-    g.threads = waves * 64;
-    g.blocks = (C + g.K - 1) / g.K;
-    g.lanes = (long long)C * NB;
-    g.scratch = (size_t)N * 4 * (size_t)g.lanes * sizeof(double);
+    g.K = K;
+    g.PC = S;
+    g.CH = sh.LPT;
+    g.threads = 64 * waves;
+    g.blocks = xcd_grid(NB > 64 ? C * ll.NBw : (C + K - 1) / K);
+    g.lanes = sh.pack();   // (SolveArgs::L)
+    g.scratch = (size_t)N * 4 * (size_t)C * NB * sizeof(double);
     return g;
+}
+
+// Segments per column: as many as bring the chip's 12 wavefronts per CU (three per
+// SIMD: 168 registers) and no more, since a second round of workgroups costs more
+// than the segments give (us, C x N x NB, FP64 by S; the first is one wavefront per CU
+// or less at S = 1):
+//   162 x 40 x 30      1: 92    2: 58    4: 38    8: 27   16: 30
+//   512 x 40 x 30      1: 93    2: 64    4: 42    8: 35   16: 58
+//   1500 x 40 x 30     1: 94    2: 81    3: 75    4: 65    8: 73
+//   1800 x 40 x 30     1: 95    2: 82    3: 76    4: 88
+//   2562 x 40 x 30     1: 121   2: 102   3: 113
+//   3200 x 40 x 30     1: 124   2: 148
+//   100 x 60 x 300     1: 141   2: 117   3: 88    4: 76    5: 109
+//   300 x 100 x 16     1: 221   4: 79    8: 58   16: 45   20: 62
+// (5 and 20 give workgroups of five wavefronts, which pack badly on four SIMDs.)  Short
+// segments give less than their hand-over costs: 48 layers take 27 in 8 segments and 29
+// in 16, 60 layers 35 and 31; 20 layers 24 in 4 and 22 in 8; 12 layers 21.7 in 4, 24 in 2.
+// Up to 4 segments, a workgroup takes as many columns as a wavefront holds groups,
+// so that its first wavefront eliminates as it goes (2562 x 40 x 30: 110 to 102,
+// mixed 91 to 76; 3000 x 60 x 16: 121 to 91); with 8 the larger workgroup costs more
+// (162 x 40 x 30: 27 to 32).
+Geometry stream_geometry(int C, int N, int NB, int NG, bool mixed, const DeviceLimits &dev)
+{
+    static constexpr struct {
+        int S, layers;
+    } splits[] = {{16, 56}, {8, 20}, {4, 8}, {3, 6}, {2, 4}};
+    const LaneLayout ll = lane_layout(NB);
+    const int n_cu = dev.n_cu > 0 ? dev.n_cu : 256;
+    const long long waves = NB > 64 ? (long long)C * ll.NBw : (C + ll.gw - 1) / ll.gw;
+    for (const auto &v : splits) {
+        if (N < v.layers || waves * v.S > 12ll * n_cu) continue;
+        const Geometry g = stream_shape(C, N, NB, NG, v.S, v.S <= 4, mixed, dev);
+        if (g.threads > 0) return g;
+    }
+    return stream_shape(C, N, NB, NG, 1, false, mixed, dev);
 }
 
 hipError_t launch_stream(const SolveArgs &a, const Geometry &g, int precision, hipStream_t s)
 {
     SolveArgs b = a;
     b.K = g.K;
+    b.PC = g.PC;
+    b.CH = g.CH;
     b.L = g.lanes;
-    const dim3 grid(g.blocks), block(g.threads);
-    if (precision != 1) hipLaunchKernelGGL((k_solve_stream<false>), grid, block, g.lds, s, b);
-    else if (a.in_f32) hipLaunchKernelGGL((k_solve_stream<true, true>), grid, block, g.lds, s, b);
-    else hipLaunchKernelGGL((k_solve_stream<true>), grid, block, g.lds, s, b);
+    with_kernel(precision, a.in_f32, g.PC > 1, [&](auto mixed, auto in32, auto seg) {
+        hipLaunchKernelGGL((k_solve_stream<decltype(mixed)::value, decltype(in32)::value, decltype(seg)::value>),
+                           dim3(g.blocks), dim3(g.threads), g.lds, s, b);
+    });
+    if (a.NB > 64) hipLaunchKernelGGL(k_stream_columns, dim3(a.C), dim3(kColumnThreads), 0, s, b);
     return hipGetLastError();
 }
 
 hipError_t launch_stream_batch(const SolveArgs *d_reqs, const int *d_first, int n, int total_blocks,
-                               const Geometry &g, int precision, int in_f32, hipStream_t s)
+                               const Geometry &g, int NB, int precision, int in_f32, hipStream_t s)
 {
-    const dim3 grid(total_blocks), block(g.threads);
-    if (precision != 1) hipLaunchKernelGGL((k_solve_stream_batch<false>), grid, block, g.lds, s, d_reqs, d_first, n);
-    else if (in_f32) hipLaunchKernelGGL((k_solve_stream_batch<true, true>), grid, block, g.lds, s, d_reqs, d_first, n);
-    else hipLaunchKernelGGL((k_solve_stream_batch<true>), grid, block, g.lds, s, d_reqs, d_first, n);
+    with_kernel(precision, in_f32, g.PC > 1, [&](auto mixed, auto in32, auto seg) {
+        hipLaunchKernelGGL((k_solve_stream_batch<decltype(mixed)::value, decltype(in32)::value, decltype(seg)::value>),
+                           dim3(total_blocks), dim3(g.threads), g.lds, s, d_reqs, d_first, n);
+    });
+    if (NB > 64)
+        hipLaunchKernelGGL(k_stream_columns_batch, dim3(total_blocks), dim3(kColumnThreads), 0, s, d_reqs, d_first, n);
     return hipGetLastError();
 }
 
 hipError_t prepare_stream_kernels(const DeviceLimits &dev)
 {
-    const void *fns[] = {reinterpret_cast<const void *>(&k_solve_stream<false>),
-                         reinterpret_cast<const void *>(&k_solve_stream<true>),
-                         reinterpret_cast<const void *>(&k_solve_stream<true, true>),
-                         reinterpret_cast<const void *>(&k_solve_stream_batch<false>),
-                         reinterpret_cast<const void *>(&k_solve_stream_batch<true>),
-                         reinterpret_cast<const void *>(&k_solve_stream_batch<true, true>)};
-    for (const void *f : fns) {
-        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dev.lds);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    hipError_t e = hipSuccess;
+    for (int v = 0; v < 6; ++v)
+        with_kernel(v > 1, v > 3, v & 1, [&](auto mixed, auto in32, auto seg) {
+            constexpr bool M = decltype(mixed)::value, I = decltype(in32)::value, G = decltype(seg)::value;
+            const void *fns[] = {reinterpret_cast<const void *>(&k_solve_stream<M, I, G>),
+                                 reinterpret_cast<const void *>(&k_solve_stream_batch<M, I, G>)};
+            for (const void *f : fns)
+                if (e == hipSuccess)
+                    e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dev.lds);
+        });
+    return e != hipSuccess ? e : upload_planck_table();
 }
 
 }  // namespace rtk

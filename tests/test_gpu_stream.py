@@ -1,8 +1,8 @@
-"""GPU parity of the wavefront-per-lanes solve, which the default tile takes on
-grids that fill the chip: lane counts on both sides of every padding step (8,
+"""GPU parity of the wavefront-per-lanes solve, the default tile's: lane counts on both sides of every padding step (8,
 16, 32, 64 lanes per column, several wavefronts per column), layer counts around
 its chunks of eight and its pairs, ragged last workgroups, Gaussian points and
-the sub-layer grid.  Bars as in ``test_gpu_parity.py``: FP64 <= 1e-10, mixed <=
+the sub-layer grid, on grids that fill the chip (one segment per column) and on
+smaller ones (2 to 16 segments).  Bars as in ``test_gpu_parity.py``: FP64 <= 1e-10, mixed <=
 1e-5 against the oracle's extended-precision build on a sample of columns."""
 import numpy as np
 import pytest
@@ -61,3 +61,33 @@ def test_stream_sublayer_grid(rt, torch):
     C = columns(30)
     w = synth.make_sublayer(synth.Spec(name="st", g_level=4, n_layers=5, n_bins=30, cloud="night", seed=741), n_cols=C)
     run(rt, torch, w, np.array([0, C // 2, C - 1]), sub=True)
+
+
+# (lanes, layers, columns) by segments per column: the fewest layers of each rule, uneven
+# splits, ragged last workgroups, a segment's groups within and across wavefronts, wide
+# columns; then grids whose size sets the number
+SEGMENTS = [(7, 57, 3), (16, 56, 5), (30, 61, 2),          # 16
+            (30, 20, 3), (30, 41, 5), (64, 23, 2), (65, 55, 2), (300, 21, 1), (5, 25, 9),   # 8
+            (30, 8, 5), (7, 12, 11), (100, 19, 2),         # 4
+            (30, 7, 3), (9, 6, 9),                         # 3
+            (30, 4, 3), (8, 5, 17),                        # 2
+            (30, 40, 1500), (30, 41, 1800), (30, 43, 2501), (100, 11, 700)]
+
+
+@pytest.mark.parametrize("NB,N,C", SEGMENTS)
+def test_stream_segments(rt, torch, NB, N, C):
+    print(f"\n[stream] {C}x{N}x{NB}", flush=True)
+    w = synth.make(synth.Spec(name="sg", g_level=4, n_layers=N, n_bins=NB, cloud="night", seed=760 + N), n_cols=C)
+    run(rt, torch, w, np.unique(np.array([0, C // 2, C - 1])))
+
+
+@pytest.mark.parametrize("NB,NG,N", [(5, 4, 21), (9, 8, 13)])
+def test_stream_segments_gauss_points(rt, torch, NB, NG, N):
+    w = synth.make_kdist(synth.Spec(name="sg", g_level=4, n_layers=N, n_bins=NB, cloud="night", seed=781),
+                         n_cols=5, n_gauss=NG)
+    run(rt, torch, w, np.arange(5), gw=w["gauss_w"])
+
+
+def test_stream_segments_sublayer_grid(rt, torch):
+    w = synth.make_sublayer(synth.Spec(name="sg", g_level=4, n_layers=23, n_bins=30, cloud="night", seed=791), n_cols=5)
+    run(rt, torch, w, np.arange(5), sub=True)
