@@ -7,14 +7,19 @@
 // means of centre and interface values), Appendix C (Rayleigh cross
 // sections of H2 and He).
 //
-// One wavefront per (slab, column) cell: the cell's k-table bracket (grid
-// cell and interpolation weights in temperature and log pressure) is the same
-// for all of the cell's outputs (bin x Gaussian point) and is found once, as
-// wavefront-uniform values; the lanes then take the outputs 64 at a time, the
-// point index fastest, so consecutive lanes read consecutive k-table entries
-// of the same (T, p) cell and write consecutive outputs.  FP64 throughout.
+// The outputs are three doubles per cell and (bin, Gaussian point), and the time that
+// writing them takes is the floor.  A workgroup takes a run of slabs of one column, a
+// thread one output of each, the point index fastest: consecutive lanes read
+// consecutive k-table entries of the same (T, p) cell and write consecutive outputs, a
+// slab's row is written at once, and neighbouring columns share an XCD.  The first
+// wavefront finds the k-table brackets of all its levels, one lane each; a bin's
+// constants stay in registers over the slabs, and a sub-layer takes the values of its
+// upper level from the slab below it.  2562 columns, 40 layers on the sub-layer grid, 600
+// outputs (2.95 GB): 642 us; a wavefront per cell, which evaluated every level twice,
+// took 1070; the best order of the stores alone takes 452.  FP64 throughout.
 #include "rt_internal.hpp"
 
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
@@ -35,10 +40,6 @@ __device__ __forceinline__ int bracket(const double *grid, int n, double &x)
     return lo;
 }
 
-struct Props {
-    double kext, w0, g0;   // extinction per unit mass, albedo, asymmetry
-};
-
 // A (T, p) point's k-table cell: lower corner (i, j) and weights (t, u).
 struct Cell {
     int i, j;
@@ -56,74 +57,109 @@ __device__ __forceinline__ Cell cell_at(const OpticsArgs &a, double T, double p)
     return q;
 }
 
-// Properties of output bg (bin b) in the k-table cell q: bilinear opacity, then
-// the mixing of gas and condensate extinction and scattering.
-__device__ __forceinline__ Props props_at(const OpticsArgs &a, const Cell &q, int bg, int b)
+constexpr int kOpticsThreads = 768;   // workgroup size bound: the most lanes of a column
+constexpr int kXcds = 8;
+constexpr int kOpticsColumns = 1 << 20;   // of one z of the grid (its threads along x: below 2^32)
+constexpr int kOpticsLevels = 64;   // of a workgroup: a lane of its first wavefront each
+
+// L slabs of a column per workgroup, 64 outputs of each per wavefront
+template <bool SUB>
+__global__ void __launch_bounds__(kOpticsThreads) k_optics(const OpticsArgs a, const int L)
 {
-    const double t = q.t, u = q.u;
+    // workgroups go to the eight XCDs in turn: each XCD takes a run of the columns of
+    // this blockIdx.z
+    const int per = gridDim.x / kXcds;
+    const int c = blockIdx.z * kOpticsColumns + (blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
+    if (c >= a.C) return;
+    const int s0 = blockIdx.y * L, n = min(L, a.S - s0);
+    // this thread's output; the padding takes the last one and stores the same values
+    const int bg = min((int)threadIdx.x, a.NBG - 1);
     const long long row = (long long)a.nT * a.NBG;
-    const double *k0 = a.kappa + (long long)q.j * row + (long long)q.i * a.NBG + bg;
-    const double k00 = k0[0], k10 = k0[a.NBG], k01 = k0[row], k11 = k0[row + a.NBG];
-    const double kap = (1 - t) * (1 - u) * k00 + t * (1 - u) * k10 + (1 - t) * u * k01 + t * u * k11;
-    const double sg = a.sig_gas[b], sa = a.sig_cl_abs[b], ss = a.sig_cl_scat[b];
-    const double scat = sg + ss;
-    const double ext = scat + kap * a.m_mean + sa;   // per gas molecule
-    Props r;
-    r.kext = ext / a.m_mean;
-    r.w0 = ext > 0.0 ? scat / ext : 0.0;
-    r.g0 = scat > 0.0 ? ss * a.g0_cl[b] / scat : 0.0;
-    return r;
-}
-
-constexpr int kOpticsThreads = 64;
-
-__device__ __forceinline__ void optics_cell(const OpticsArgs &a, const long long cell)
-{
-    const int s = (int)(cell / a.C), c = (int)(cell - (long long)s * a.C);
-    // the cell's values: uniform across the wavefront
-    Cell q0, q1;
-    double dp;
-    if (!a.sub) {
-        q0 = cell_at(a, a.Tc[(long long)s * a.C + c], a.pc[(long long)s * a.C + c]);
-        q1 = q0;
-        dp = a.p[(long long)s * a.C + c] - a.p[(long long)(s + 1) * a.C + c];
-    } else {
-        // sub-layer s between levels s and s+1: even levels interfaces, odd ones centres
-        auto lev = [&](int l, double &T, double &p) {
-            const long long o = (long long)(l >> 1) * a.C + c;
+    // levels of the slabs, one lane each: centres, or on the sub-layer grid the lower
+    // level and then the upper ones (even levels interfaces, odd ones centres)
+    __shared__ struct Level {
+        double w00, w10, w01, w11;   // weights of the k-table cell's corners
+        long long at;                // its lower corner
+        double scale;                // optical depth of the slab above per extinction
+    } levels[kOpticsLevels];
+    if (threadIdx.x < 64) {
+        const int ln = threadIdx.x, l = s0 + min(ln, SUB ? n : n - 1);
+        const long long o = (long long)(SUB ? l >> 1 : l) * a.C + c;
+        double T, p, dp;
+        if constexpr (SUB) {
             T = (l & 1) ? a.Tc[o] : a.T[o];
             p = (l & 1) ? a.pc[o] : a.p[o];
-        };
-        double T0, p0, T1, p1;
-        lev(s, T0, p0);
-        lev(s + 1, T1, p1);
-        q0 = cell_at(a, T0, p0);
-        q1 = cell_at(a, T1, p1);
-        dp = p0 - p1;
-    }
-    for (int bg = threadIdx.x; bg < a.NBG; bg += kOpticsThreads) {
-        const int b = bg / a.NG;
-        Props P;
-        if (!a.sub) {
-            P = props_at(a, q0, bg, b);
+            dp = 0.5 * (p - __shfl_down(p, 1));   // of both levels' mean
         } else {
-            const Props A = props_at(a, q0, bg, b), B = props_at(a, q1, bg, b);
-            P.kext = 0.5 * (A.kext + B.kext);
-            P.w0 = 0.5 * (A.w0 + B.w0);
-            P.g0 = 0.5 * (A.g0 + B.g0);
+            T = a.Tc[o];
+            p = a.pc[o];
+            dp = a.p[o] - a.p[o + a.C];
         }
-        const long long e = cell * a.NBG + bg;
-        a.dtau[e] = P.kext * dp / a.gravity;
-        a.w0[e] = P.w0;
-        a.g0[e] = P.g0;
+        const Cell q = cell_at(a, T, p);
+        levels[ln] = {(1 - q.t) * (1 - q.u), q.t * (1 - q.u), (1 - q.t) * q.u, q.t * q.u,
+                      q.j * row + (long long)q.i * a.NBG, dp / a.gravity / a.m_mean};
     }
-}
-
-__global__ void __launch_bounds__(kOpticsThreads) k_optics(const OpticsArgs a)
-{
-    // cell = s C + c, over a grid of rows of gridDim.x workgroups
-    const long long cell = (long long)blockIdx.y * gridDim.x + blockIdx.x;
-    if (cell < (long long)a.S * a.C) optics_cell(a, cell);
+    const int b = bg / a.NG;
+    const double ss = a.sig_cl_scat[b], sa = a.sig_cl_abs[b], scat = a.sig_gas[b] + ss;
+    const double g0 = scat > 0.0 ? ss * a.g0_cl[b] / scat : 0.0;
+    struct Corners {
+        double k00, k10, k01, k11;
+    };
+    auto load = [&](int k) -> Corners {
+        const int kc = SUB ? min(k, n) : min(k, n - 1);
+        const long long e = levels[kc].at;
+        const double *k0 = a.kappa + ((long long)__builtin_amdgcn_readfirstlane((int)(e >> 32)) << 32 |
+                                      (unsigned)__builtin_amdgcn_readfirstlane((int)e));
+        return {k0[bg], (k0 + a.NBG)[bg], (k0 + row)[bg], (k0 + row + a.NBG)[bg]};
+    };
+    // extinction per gas molecule and albedo at level k: bilinear opacity, then the
+    // mixing of gas and condensate extinction and scattering
+    double ext_lo = 0.0, w0_lo = 0.0;
+    auto level = [&](int k, const Corners &v, double &ext, double &w0) {
+        const Level &m = levels[k];
+        const double kap = m.w00 * v.k00 + m.w10 * v.k10 + m.w01 * v.k01 + m.w11 * v.k11;
+        ext = scat + kap * a.m_mean + sa;
+        w0 = ext > 0.0 ? scat / ext : 0.0;
+    };
+    auto store = [&](int k, double dtau, double w0) {
+        const long long e = ((long long)(s0 + k) * a.C + c) * a.NBG;
+        (a.dtau + e)[bg] = dtau;
+        (a.w0 + e)[bg] = w0;
+        (a.g0 + e)[bg] = g0;
+    };
+    // slab k from level k + SUB's opacities; the next but one level's loads go out
+    // before this slab's stores, into the same registers
+    auto slab = [&](int k, Corners &v) {
+        double ext, w0;
+        level(k + SUB, v, ext, w0);
+        v = load(k + SUB + 2);
+        if constexpr (SUB) {
+            store(k, (ext_lo + ext) * levels[k].scale, 0.5 * (w0_lo + w0));
+            ext_lo = ext;
+            w0_lo = w0;
+        } else {
+            store(k, ext * levels[k].scale, w0);
+        }
+    };
+    __syncthreads();
+    Corners x = load(0), y = load(1);
+    if constexpr (SUB) {
+        level(0, x, ext_lo, w0_lo);
+        x = load(2);
+        int k = 0;
+        for (; k + 2 <= n; k += 2) {
+            slab(k, y);
+            slab(k + 1, x);
+        }
+        if (k < n) slab(k, y);
+    } else {
+        int k = 0;
+        for (; k + 2 <= n; k += 2) {
+            slab(k, x);
+            slab(k + 1, y);
+        }
+        if (k < n) slab(k, x);
+    }
 }
 
 // Gauss-Legendre nodes and weights on [-1, 1] by Newton iteration on the
@@ -197,12 +233,22 @@ double rayleigh_bin_average(double lam_lo, double lam_hi, double x_h2, double x_
 
 hipError_t launch_optics(const OpticsArgs &a, hipStream_t s)
 {
-    const long long cells = (long long)a.S * a.C;
-    if (cells == 0 || a.NBG == 0) return hipSuccess;
-    // one workgroup per cell: rows of up to 2^30 workgroups
-    const long long row = cells < (1LL << 30) ? cells : (1LL << 30);
-    const long long rows = (cells + row - 1) / row;
-    hipLaunchKernelGGL(k_optics, dim3((unsigned)row, (unsigned)rows), dim3(kOpticsThreads), 0, s, a);
+    if ((long long)a.S * a.C == 0 || a.NBG == 0) return hipSuccess;
+    // Slabs per workgroup, in even runs of at most 16: longer ones spread the stores in
+    // flight over more of the memory's pages (2562 columns, 80 slabs x 600 outputs, us by
+    // slabs: 4: 905, 8: 716, 16: 642, 27: 724, 40: 783; stores alone 562, 631, 700, -, 760),
+    // shorter ones pay for a workgroup's start, about 6 us, too often (30 outputs: 4: 91,
+    // 16: 57, 40: 54).  Fewer, from 4 on, where that leaves the chip idle: six wavefronts per
+    // CU, and three workgroups per two CUs (162 columns, 30 outputs: 4: 10.4, 8: 9.4, 16:
+    // 10.2, 40: 14.3).
+    const int waves = (a.NBG + 63) / 64;
+    const long long n_cu = 256, want = std::max(n_cu * 6 / waves, n_cu * 3 / 2);
+    const long long least = std::min<long long>((a.S + 3) / 4, (want + a.C - 1) / a.C);
+    const int runs = (int)std::max<long long>((a.S + 15) / 16, least), L = (a.S + runs - 1) / runs;
+    const int columns = std::min(a.C, kOpticsColumns);
+    const dim3 grid((columns + kXcds - 1) / kXcds * kXcds, (a.S + L - 1) / L, (a.C + kOpticsColumns - 1) / kOpticsColumns);
+    if (a.sub) hipLaunchKernelGGL(k_optics<true>, grid, dim3(64 * waves), 0, s, a, L);
+    else hipLaunchKernelGGL(k_optics<false>, grid, dim3(64 * waves), 0, s, a, L);
     return hipGetLastError();
 }
 

@@ -63,6 +63,24 @@ def test_optics_elementwise(rt, torch, NB, NG, sublayer):
     s.close()
 
 
+# runs of slabs around their longest (16) and the shortest split, columns around the eight
+# XCDs' shares, outputs around a wavefront and the widest column
+@pytest.mark.parametrize("C,N,NB,NG", [(1, 1, 1, 1), (7, 3, 64, 1), (9, 17, 65, 1), (390, 16, 5, 1), (1300, 17, 3, 2),
+                                       (400, 19, 24, 16), (3, 33, 32, 24)])
+@pytest.mark.parametrize("sublayer", [False, True])
+def test_optics_runs(rt, torch, C, N, NB, NG, sublayer):
+    atm, tab, gw, s = setup(rt, C=C, N=N, NB=NB, NG=NG, seed=320 + N)
+    print(f"\n[optics] {C}x{N}x{NB}x{NG} sublayer={sublayer}", flush=True)
+    out = s.optical_properties(device_atm(torch, atm), sublayer=sublayer)
+    torch.cuda.synchronize()
+    ref = O.optics(atm, tab, sublayer=sublayer)
+    g = {k: v.cpu().numpy() for k, v in out.items()}
+    assert np.max(np.abs(g["dtau"] - ref["dtau"]) / np.maximum(ref["dtau"], 1e-300)) <= OPTICS_REL
+    for k in ("w0", "g0"):
+        assert np.max(np.abs(g[k] - ref[k])) <= OPTICS_ABS, k
+    s.close()
+
+
 def test_optics_then_solve(rt, torch):
     """The paper's production pipeline shape in small: k-table bins with
     Gaussian points on the sub-layer grid, optics then fluxes, against the
