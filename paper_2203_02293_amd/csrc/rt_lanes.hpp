@@ -80,6 +80,12 @@ __device__ __forceinline__ void uniform_value(T &x)
     asm volatile("" : "+s"(x));
 }
 
+// A value that all lanes hold, in scalar registers.
+__device__ __forceinline__ double first_lane(double x)
+{
+    return __hiloint2double(wave_uniform(__double2hiint(x)), wave_uniform(__double2loint(x)));
+}
+
 // The options used per layer, read anew here and kept in scalar registers.
 __device__ __forceinline__ Opts uniform_options(ArgsK ap)
 {
@@ -110,16 +116,18 @@ __device__ __forceinline__ double level_T(const SolveArgs &a, bool sub, int l, i
 }
 
 // Bin radiance at temperature Td from the edge integrals re[0], re[1] of the
-// bin; c2b, c2a: c2 / lambda at its edges (LDS), fb, fa the same in FP32.
+// bin; c2b, c2a: c2 / lambda at its edges (LDS), fb, fa the same in FP32.  narrow (MIXED):
+// all bins are (planck_narrow), and there are no edge integrals.
 template <bool MIXED, class R>
-__device__ __forceinline__ R bin_radiance(const R *re, double Td, float fb, float fa, const double *c2)
+__device__ __forceinline__ R bin_radiance(const R *re, double Td, float fb, float fa, const double *c2, bool narrow)
 {
     const R Tr = R(Td), T2 = Tr * Tr;
-    R I = planck_combine<R>(re[0], re[1]);
+    R I = R(0);
+    if (!MIXED || !narrow) I = planck_combine<R>(re[0], re[1]);
     if constexpr (MIXED) {
         const R iT = rcp(Tr);
         const R xb = fb * iT, xa = fa * iT;
-        if (planck_narrow(xa, xb)) {
+        if (narrow || planck_narrow(xa, xb)) {
             const double iTd = rcp(Td);
             I = planck_gl3(c2[1] * iTd, c2[0] * iTd);
         }

@@ -160,13 +160,12 @@ struct ExpTail8 {
     static constexpr double coef(int j) { return inv_fact(j + 1); }
 };
 
-template <>
-__host__ __device__ __forceinline__ ExpEm1<float> exp_em1<float>(float x)
+// (of an argument in [-104, 88])
+__host__ __device__ __forceinline__ ExpEm1<float> exp_em1_in_range(float x)
 {
     constexpr float L = 1.44269502162933349609375f;                // log2 e rounded to FP32
     constexpr float LLO = float(1.44269504088896340736 - 1.44269502162933349609375);
     constexpr float LN2 = 0.693147180559945309f;
-    x = fminf(fmaxf(x, -104.0f), 88.0f);
     const float y = x * L;
     const float yl = fmaf(x, LLO, fmaf(x, L, -y));
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -181,6 +180,12 @@ __host__ __device__ __forceinline__ ExpEm1<float> exp_em1<float>(float x)
     return out;
 }
 
+template <>
+__host__ __device__ __forceinline__ ExpEm1<float> exp_em1<float>(float x)
+{
+    return exp_em1_in_range(fminf(fmaxf(x, -104.0f), 88.0f));
+}
+
 // e^x in FP32 for an FP64 argument: the FP32 exponential of the rounded
 // argument, times 1 + (its rounding error).  A large argument thus keeps the
 // relative accuracy of FP32 (an argument rounded to FP32 costs |x| 2^-24 of
@@ -190,7 +195,7 @@ __host__ __device__ __forceinline__ ExpEm1<float> exp_em1_f(double x)
     x = fmin(fmax(x, -104.0), 88.0);
     const float xh = float(x);
     const float xl = float(x - double(xh));
-    ExpEm1<float> e = exp_em1(xh);
+    ExpEm1<float> e = exp_em1_in_range(xh);
     e.em1 = fmaf(e.e, xl, e.em1);
     e.e = fmaf(e.e, xl, e.e);
     return e;

@@ -216,8 +216,12 @@ __host__ __device__ __forceinline__ float planck_gl3(double xa, double xb)
     const float ws[3] = {float(5.0 / 9.0), float(8.0 / 9.0), float(5.0 / 9.0)};
     float acc = 0.0f;
     for (int i = 0; i < 3; ++i) {
-        const ExpEm1<float> e = exp_em1_f(-xs[i]);   // t^3 e^-t / (1 - e^-t)
-        const float xf = float(xs[i]);
+        // t^3 e^-t / (1 - e^-t); exp_em1_f(-t) from the one FP32 rounding of t
+        const float xf = float(xs[i]), xh = fminf(fmaxf(-xf, -104.0f), 88.0f);
+        const float xl = float(fmin(fmax(-xs[i], -104.0), 88.0) - double(xh));
+        ExpEm1<float> e = exp_em1_in_range(xh);
+        e.em1 = fmaf(e.e, xl, e.em1);
+        e.e = fmaf(e.e, xl, e.e);
         acc += ws[i] * xf * xf * xf * e.e * rcp(-e.em1);
     }
     return float(h) * acc;
@@ -231,11 +235,26 @@ __host__ __device__ __forceinline__ float planck_gl3(double xa, double xb)
 // values are at most pi^4/15 (large x: x^3 e^-x (1 + 3/x + ...)) against an
 // integral of about (xb - xa) times the integrand: xb - xa <= 0.3 bounds the
 // ratio by ~16.
+// (PlanckNarrow, below, is the range of temperatures at which that holds for sure.)
 template <class R>
 __host__ __device__ __forceinline__ bool planck_narrow(R xa, R xb)
 {
     if (xb > PCfg<R>::XS) return xb - xa <= R(0.3);
     return xa * xa * xa > R(0.9375) * (xb * xb * xb);
+}
+
+// Temperatures in [lo, hi] at which planck_narrow in FP32 is true of a bin for sure; cb >
+// ca are its edges' c2 / lambda.  The margins are those of its FP32 roundings: 1e-6 of x, and
+// the cubes of x far from underflow.
+struct PlanckNarrow {
+    double lo, hi;
+};
+__host__ __device__ __forceinline__ PlanckNarrow planck_narrow_range(double ca, double cb)
+{
+    const double q = ca / cb;
+    const bool ratio = q * q * q > 0.9375 * (1.0 + 1e-5);
+    const double top = ca * 1e9, above = cb * (1.0 / (PCfg<float>::XS * (1.0 + 1e-5)));
+    return {(cb - ca + 1e-6 * cb) * (1.0 / 0.299), ratio ? top : (above < top ? above : top)};
 }
 
 // ---------------------------------------------------------------------------
@@ -403,9 +422,10 @@ __host__ __device__ __forceinline__ void layer_terms(R dtau, R w0, R g0, R E, R 
             R i1s = rcp(one + s);
             R X = (Qc - c1 * ik * rcp(one + lm)) * i1s;
             R Yh = (Qc * (a - lam) - c1 * a * ik) * i1s;
-            R dq = (a >= lam) ? Tr * phi1((a - lam) * dtau) : beta * phi1((lam - a) * dtau);
+            // (one phi1 for both signs of a - lam: lanes fall on both sides)
+            R dq = (a >= lam ? Tr : beta) * phi1(R(fabs(a - lam)) * dtau);
             R Z = Yh * dq * dtau;
-            R rho = zm * rcp(zp);
+            R rho = zm * (R(2) * i1s);              // 1 / zp
             R iom = (zp * zp) * rcp(s * den);       // 1 / (1 - rho^2 T^2)
             R obt = omB + beta * omT;               // 1 - beta T
             sb_up = Fup * (rho * Tr * Z - X * obt) * iom;

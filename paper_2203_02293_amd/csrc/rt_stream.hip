@@ -93,21 +93,15 @@ __host__ __device__ __forceinline__ StreamLds stream_lds(const StreamShape &sh, 
     return o;
 }
 
-// Where a slice of a wide column leaves its level sums and flags for
-// k_stream_columns: value t (up, down, beam of level t / 3, then the flags) runs
-// through its records' planes, as many values in each as the last, shortest slice has
-// doubles there.  (The lanes' F_up at the TOA take the last plane.)
-struct SliceValues {
-    int per;
-    __device__ __forceinline__ double *at(double *rec, long long LB, int t) const
-    {
-        const int plane = small_div(t, per);
-        return rec + plane * LB * 2 + (t - plane * per);
-    }
-};
-__device__ __forceinline__ SliceValues slice_values(int NB, const StreamShape &sh)
+// Back-substitution records: a workgroup's lanes (K columns, or a slice of one) hold
+// theirs in one block, [layer][2][lane] double2, in the order of the lanes.  (In planes of
+// all lanes the stores of thousands of wavefronts, each at its own layer, spread over
+// the memory's pages: 10242 x 80 x 300 mixed, 7.9 GB of records, @@@ ms.)  A slice of a
+// wide column leaves its level sums (up, down, beam of each level) and flags for
+// k_stream_columns at the start of its block, its lanes' F_up at the TOA in the last plane.
+__device__ __forceinline__ double2 *record_block(double *scratch, int N, int NB, int c, int lane0)
 {
-    return {2 * (NB - (sh.NBw - 1) * sh.NBs)};
+    return reinterpret_cast<double2 *>(scratch) + ((long long)c * NB + lane0) * 2 * N;
 }
 
 // The elimination's map of (c, eps = 1 - c, d) over a run of layers.  With den = (1 - r)
@@ -260,10 +254,15 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
 
     const long long LB = (long long)C * NB;
     const unsigned lane = (unsigned)c * NB + b;   // of a [C][NB] plane
+    auto records = [&]() -> double2 * { return record_block(args().scratch, N, NB, c0, lane0); };
     // byte offsets of this lane's layers from those of the lowest segment (32 bits: stream_geometry)
     const int a_last = SEG ? N - LPT : 0;
+    // records: lanes of the workgroup's block, this one's place in it
+    const int RB = wide ? nlane : min(K, C - c0) * NB;
+    const unsigned rlane = wide ? b - lane0 : (c - c0) * NB + b;
+    const unsigned rlay = SEG ? (unsigned)(a_last - me.a) * (unsigned)RB : 0u;
     const unsigned lay = SEG ? (unsigned)(a_last - me.a) * (unsigned)LB : 0u;
-    const unsigned o_in = (lane + lay) * (unsigned)sizeof(InT), o_rec = lane * 16u + lay * 32u;
+    const unsigned o_in = (lane + lay) * (unsigned)sizeof(InT), o_rec = rlane * 16u + rlay * 32u;
     auto in_at = [&](const double *base, int q) -> InT {   // step q's (past the last: one of the lowest layers, unused)
         return at(reinterpret_cast<const InT *>(base) + (long long)max(N - 1 - a_last - q, 0) * LB, o_in);
     };
@@ -349,11 +348,30 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
         sync();
     }
 
+    // Mixed: temperatures at which every bin of the wavefront takes the narrow bins'
+    // quadrature; a chunk of such levels needs no edge integrals (300 bins: all of them;
+    // 10242 x 80 x 300: @@@ ms).
+    double narrow_lo = 0.0, narrow_hi = 0.0;
+    bool narrow = false;
+    if constexpr (MIXED) {
+        const PlanckNarrow r = planck_narrow_range(args().c2_over_lam[bin + 1], args().c2_over_lam[bin]);
+        narrow_lo = r.lo;
+        narrow_hi = r.hi;
+#pragma unroll
+        for (int m = 1; m < 64; m <<= 1) {
+            narrow_lo = fmax(narrow_lo, __shfl_xor(narrow_lo, m));
+            narrow_hi = fmin(narrow_hi, __shfl_xor(narrow_hi, m));
+        }
+        narrow_lo = first_lane(narrow_lo);
+        narrow_hi = first_lane(narrow_hi);
+    }
     auto edges = [&](double T, int from, int n, bool check) {
+        if constexpr (MIXED) narrow = !wave_any(!(T >= narrow_lo && T <= narrow_hi));
         if (rq >= from && rq < n) {
             if (check && (!(T > 0.0) || !isfinite(T))) atomicOr(&s_flag[rg.kk], (uint32_t)F_INVALID);
             const double iT = rcp(T);
             if (e0 == 0) s_T[row] = T;
+            if (!MIXED || !narrow) {
             // two at a time (past the last edge: that one again), so that their chains overlap
             R *re = s_edge + row * lo.estride;
             for (int i = 0; i < ne; i += 2 * epr) {
@@ -362,12 +380,13 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
                 re[e1] = v1;
                 re[e2] = v2;
             }
+            }
         }
         wave_sync();
     };
     auto bin_B = [&](int q) -> R {
         const int rw = gl * kChunk + q;
-        return bin_radiance<MIXED, R>(s_edge + rw * lo.estride + rb, s_T[rw], c2fb, c2fa, s_c2 + bin);
+        return bin_radiance<MIXED, R>(s_edge + rw * lo.estride + rb, s_T[rw], c2fb, c2fa, s_c2 + bin, narrow);
     };
     // Column sums of n rows of lane values v (LDS, kSumStride apart) into the sums of
     // levels lev(group, row): lane (q, p) = (ln % 8, ln / 8) adds the 8 lanes p of row
@@ -434,10 +453,10 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
         // (the layer that a shorter segment repeats is another's: that step stores in
         // the place of the next one)
         const bool first = SEG && uneven && q == 0;
-        const unsigned o_st = o_rec + (first && me.a == me.e ? (unsigned)LB * 32u : 0u);
-        double2 *p_rec = reinterpret_cast<double2 *>(args().scratch) + (long long)(N - 1 - a_last - q - (first ? 1 : 0)) * 2 * LB;
+        const unsigned o_st = o_rec + (first && me.a == me.e ? (unsigned)RB * 32u : 0u);
+        double2 *p_rec = records() + (long long)(N - 1 - a_last - q - (first ? 1 : 0)) * 2 * RB;
         at(p_rec, o_st) = x;
-        at(p_rec + LB, o_st) = y;
+        at(p_rec + RB, o_st) = y;
         if (wday) s_val[v * kSumStride + ln] = wgt * Fb_lo;
         Fb_up = Fb_lo;
         Bup = B;
@@ -500,11 +519,10 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
         constexpr int RC = 4;
         double2 x[RC], y[RC];
         auto ld = [&](int q, int k) {
-            const double2 *r = reinterpret_cast<const double2 *>(args().scratch) +
-                               (long long)(N - 1 - a_last - min(q, LPT - 1)) * 2 * LB;
+            const double2 *r = records() + (long long)(N - 1 - a_last - min(q, LPT - 1)) * 2 * RB;
             x[k] = at(r, o_rec);
-            if constexpr (MIXED) y[k].x = at(r + LB, o_rec).x;
-            else y[k] = at(r + LB, o_rec);
+            if constexpr (MIXED) y[k].x = at(r + RB, o_rec).x;
+            else y[k] = at(r + RB, o_rec);
         };
         double gam = 1.0, eta = 0.0;
         auto step = [&](int q, int k) {
@@ -518,9 +536,9 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
                 unpack_tra(x[k], t, r, A);
                 rec = elim_step(st, t, r, t + A, A, y[k].x, y[k].y);
             }
-            double2 *r = reinterpret_cast<double2 *>(args().scratch) + (long long)(N - 1 - a_last - q) * 2 * LB;
+            double2 *r = records() + (long long)(N - 1 - a_last - q) * 2 * RB;
             at(r, o_rec) = make_double2(rec.G, rec.H);
-            at(r + LB, o_rec) = make_double2(rec.c, rec.d);
+            at(r + RB, o_rec) = make_double2(rec.c, rec.d);
             eta = fma(gam, rec.H, eta);
             gam *= rec.G;
         };
@@ -574,14 +592,14 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
     int jn = first - 1;   // next record: that of the layer below the level
     auto ld = [&](int k) {
         if constexpr (SEG) {
-            const unsigned q = lane * 16u + (unsigned)max(min(jn, last - 1), 0) * (unsigned)LB * 32u;
-            const double2 *r = reinterpret_cast<const double2 *>(args().scratch);
+            const unsigned q = rlane * 16u + (unsigned)max(min(jn, last - 1), 0) * (unsigned)RB * 32u;
+            const double2 *r = records();
             r0[k] = at(r, q);
-            r1[k] = at(r + LB, q);
+            r1[k] = at(r + RB, q);
         } else {
-            const double2 *r = reinterpret_cast<const double2 *>(args().scratch) + (long long)max(min(jn, N - 1), 0) * 2 * LB;
+            const double2 *r = records() + (long long)max(min(jn, N - 1), 0) * 2 * RB;
             r0[k] = at(r, o_rec);
-            r1[k] = at(r + LB, o_rec);
+            r1[k] = at(r + RB, o_rec);
         }
         ++jn;
     };
@@ -634,12 +652,11 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
         }
         write_columns(ap, c0, K, s_flag, [&](int l, int v, int k) { return s_sum[(3 * l + v) * K + k]; });
     } else {
-        // this slice's sums and flags in the place of its used records (slice_value)
-        double *rec = args().scratch + ((long long)c0 * NB + lane0) * 2;
-        const SliceValues sv = slice_values(NB, sh);
-        for (int t = tid; t < 3 * (N + 1); t += W) *sv.at(rec, LB, t) = t % 3 == 2 && !wday ? 0.0 : s_sum[t];
-        if (tid == 0) *sv.at(rec, LB, 3 * (N + 1)) = (double)s_flag[0];
-        if (act && me.s == 0 && NG > 1) rec[(2 * N - 1) * LB * 2 + (b - lane0)] = Fu_toa;
+        // this slice's sums and flags in the place of its used records
+        double *rec = reinterpret_cast<double *>(records());
+        for (int t = tid; t < 3 * (N + 1); t += W) rec[t] = t % 3 == 2 && !wday ? 0.0 : s_sum[t];
+        if (tid == 0) rec[3 * (N + 1)] = (double)s_flag[0];
+        if (act && me.s == 0 && NG > 1) rec[(2 * N - 1) * RB * 2 + (b - lane0)] = Fu_toa;
     }
 }
 
@@ -651,10 +668,10 @@ __device__ __forceinline__ void solve_columns(ArgsK ap, const int c)
     auto args = [&]() -> const SolveArgs & { return *(const SolveArgs *)ap; };
     const int NB = args().NB, NG = args().NG, C = args().C, N = args().N, tid = threadIdx.x;
     const StreamShape sh = StreamShape::unpack(args().CH, args().L);
-    const long long LB = (long long)C * NB;
-    double *rec = args().scratch + (long long)c * NB * 2;
-    const SliceValues sv = slice_values(NB, sh);
-    auto value = [&](int w, int t) -> double { return *sv.at(rec + w * sh.NBs * 2, LB, t); };
+    auto slice = [&](int w) -> const double * {
+        return reinterpret_cast<const double *>(record_block(args().scratch, N, NB, c, w * sh.NBs));
+    };
+    auto value = [&](int w, int t) -> double { return slice(w)[t]; };
     if (tid == 0) {
         uint32_t f = 0u;
         for (int w = 0; w < sh.NBw; ++w) f |= (uint32_t)value(w, 3 * (N + 1));
@@ -662,12 +679,11 @@ __device__ __forceinline__ void solve_columns(ArgsK ap, const int c)
     }
     __syncthreads();
     if (NG > 1 && args().F_up_toa_bin) {   // the spectrum: weighted sums over each bin's points
-        const double *f = rec + (2 * N - 1) * LB * 2;
         for (int r = tid; r < sh.NBR; r += blockDim.x) {
             double s = 0.0;
             for (int g = 0; g < NG; ++g) {
-                const int l = r * NG + g, w = small_div(l, sh.NBs);
-                s += args().wg[g] * f[w * sh.NBs * 2 + l - w * sh.NBs];
+                const int l = r * NG + g, w = small_div(l, sh.NBs), n = min(sh.NBs, NB - w * sh.NBs);
+                s += args().wg[g] * slice(w)[(2 * N - 1) * n * 2 + l - w * sh.NBs];
             }
             args().F_up_toa_bin[(long long)c * sh.NBR + r] = s;
         }
