@@ -96,7 +96,7 @@ __host__ __device__ __forceinline__ StreamLds stream_lds(const StreamShape &sh, 
 // Back-substitution records: a workgroup's lanes (K columns, or a slice of one) hold
 // theirs in one block, [layer][2][lane] double2, in the order of the lanes.  (In planes of
 // all lanes the stores of thousands of wavefronts, each at its own layer, spread over
-// the memory's pages: 10242 x 80 x 300 mixed, 7.9 GB of records, @@@ ms.)  A slice of a
+// the memory's pages: 10242 x 80 x 300 mixed, 7.9 GB of records, took 4.8 ms in place of 4.3.)  A slice of a
 // wide column leaves its level sums (up, down, beam of each level) and flags for
 // k_stream_columns at the start of its block, its lanes' F_up at the TOA in the last plane.
 __device__ __forceinline__ double2 *record_block(double *scratch, int N, int NB, int c, int lane0)
@@ -268,7 +268,9 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
     };
     // The inputs of a layer are loaded two layers ahead, into the registers that
     // the layer before has just used (a copy between registers would wait for
-    // the load, and with it for the record stores before it).
+    // the load, and with it for the record stores before it), from pointers that move
+    // with the layers (addresses worked out anew take twenty scalar instructions of a
+    // layer's 600, and argument loads that the wavefront waits for).
     InT dt0, w0, g0_, dt1, w1, g1;
     auto load = [&](int q, InT &dt, InT &w, InT &g) {
         dt = in_at(args().dtau, q);
@@ -279,6 +281,20 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
     const bool uneven = SEG && N % S != 0;   // some segments repeat a layer
     load(odd, dt0, w0, g0_);
     load(1 - odd, dt1, w1, g1);   // (odd: the first step, then the third in its place)
+    int left = N - 1 - a_last - 2;   // layers below that of the next load (step 2)
+    const InT *p_dt = reinterpret_cast<const InT *>(args().dtau) + (long long)max(left, 0) * LB;
+    const InT *p_w = reinterpret_cast<const InT *>(args().w0) + (long long)max(left, 0) * LB;
+    const InT *p_g = reinterpret_cast<const InT *>(args().g0) + (long long)max(left, 0) * LB;
+    auto load_next = [&](InT &dt, InT &w, InT &g) {
+        dt = at(p_dt, o_in);
+        w = at(p_w, o_in);
+        g = at(p_g, o_in);
+        const long long step = left > 0 ? LB : 0;   // (at the lowest layer: again)
+        --left;
+        p_dt -= step;
+        p_w -= step;
+        p_g -= step;
+    };
     // Planck edge integrals of a chunk of levels: rows (group of the wavefront, row of
     // the chunk); a lane keeps one row and steps through its edges, so a wavefront's
     // lanes sit in neighbouring edges and the row's temperature stays in a register.
@@ -349,8 +365,8 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
     }
 
     // Mixed: temperatures at which every bin of the wavefront takes the narrow bins'
-    // quadrature; a chunk of such levels needs no edge integrals (300 bins: all of them;
-    // 10242 x 80 x 300: @@@ ms).
+    // quadrature; a chunk of such levels needs no edge integrals (10242 x 80 x 300: 380
+    // vector instructions per layer in place of 434).
     double narrow_lo = 0.0, narrow_hi = 0.0;
     bool narrow = false;
     if constexpr (MIXED) {
@@ -408,6 +424,11 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
         wave_sync();
     };
 
+    // records: the layer that a shorter segment repeats is another's, so an uneven split's
+    // first step stores in the place of its next one, whose records follow
+    double2 *p_rec = records() + (long long)(N - 1 - a_last - (uneven ? 1 : 0)) * 2 * RB;
+    int rec_step = uneven ? 0 : 2 * RB;
+    unsigned o_st = o_rec + (uneven && me.a == me.e ? (unsigned)RB * 32u : 0u);
     Opts o;
     auto options = [&]() {   // (read anew in each chunk)
         opaque_args(ap);
@@ -426,7 +447,7 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
         }
         const Layer<R> Ly = layer_item<MIXED, R, MIXED>(dt, double(w_), double(g_), day, mu, inv_mu, Fb_up, Fb_lo,
                                                         B, Bup, o, inv_eps2, fl);
-        load(q + 2, dt_, w_, g_);
+        load_next(dt_, w_, g_);
         double2 x, y;
         if constexpr (!SEG) {
             const BackRec rec = elim_step(st, double(Ly.t), double(Ly.r), double(Ly.omr), double(Ly.A),
@@ -450,18 +471,16 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
             x = pack_tra(Ly.t, Ly.r, Ly.A);
             y = make_double2(Ly.Sup, Ly.Sdn);
         }
-        // (the layer that a shorter segment repeats is another's: that step stores in
-        // the place of the next one)
-        const bool first = SEG && uneven && q == 0;
-        const unsigned o_st = o_rec + (first && me.a == me.e ? (unsigned)RB * 32u : 0u);
-        double2 *p_rec = records() + (long long)(N - 1 - a_last - q - (first ? 1 : 0)) * 2 * RB;
         at(p_rec, o_st) = x;
         at(p_rec + RB, o_st) = y;
+        p_rec -= rec_step;
+        rec_step = 2 * RB;
+        o_st = o_rec;
         if (wday) s_val[v * kSumStride + ln] = wgt * Fb_lo;
         Fb_up = Fb_lo;
         Bup = B;
         if constexpr (SEG)
-            if (first && me.a != me.e) map = StateMap();
+            if (uneven && q == 0 && me.a != me.e) map = StateMap();
     };
     options();
     edges(Tc_, 0, min(kChunk, LPT + head - odd), rq > 0);
@@ -589,18 +608,16 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
     const int ilo = N - me.e1, first = low ? 0 : ilo + 1;   // its lowest layer, its first level
     const int last = N - me.e;                              // its last level
     double2 r0[RD], r1[RD];
-    int jn = first - 1;   // next record: that of the layer below the level
+    // next record: that of the layer below the level (past the last: the last again)
+    int jn = first - 1;
+    const double2 *p_back = records();
+    unsigned o_back = rlane * 16u;
+    if constexpr (SEG) o_back += (unsigned)max(jn, 0) * (unsigned)RB * 32u;
     auto ld = [&](int k) {
-        if constexpr (SEG) {
-            const unsigned q = rlane * 16u + (unsigned)max(min(jn, last - 1), 0) * (unsigned)RB * 32u;
-            const double2 *r = records();
-            r0[k] = at(r, q);
-            r1[k] = at(r + RB, q);
-        } else {
-            const double2 *r = records() + (long long)max(min(jn, N - 1), 0) * 2 * RB;
-            r0[k] = at(r, o_rec);
-            r1[k] = at(r + RB, o_rec);
-        }
+        r0[k] = at(p_back, o_back);
+        r1[k] = at(p_back + RB, o_back);
+        if constexpr (SEG) o_back += jn >= 0 && jn < last - 1 ? (unsigned)RB * 32u : 0u;
+        else p_back += jn >= 0 && jn < N - 1 ? 2 * RB : 0;
         ++jn;
     };
 #pragma unroll
