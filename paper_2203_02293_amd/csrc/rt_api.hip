@@ -166,7 +166,7 @@ bool prepare_once(int dev, const rtk::DeviceLimits &lim)
     std::lock_guard<std::mutex> lk(g_prepare_mu);
     if (dev >= 0 && dev < kMaxDevices && g_prepared[dev]) return true;
     if (rtk::prepare_kernels(lim) != hipSuccess || rtk::prepare_stream_kernels(lim) != hipSuccess ||
-        rtk::prepare_deep_kernels(lim) != hipSuccess)
+        rtk::prepare_deep_kernels(lim) != hipSuccess || rtk::prepare_cascade_kernels(lim) != hipSuccess)
         return false;
     if (dev >= 0 && dev < kMaxDevices) g_prepared[dev] = true;
     return true;
@@ -458,26 +458,50 @@ extern "C" rt_status rt_destroy(rt_handle *h)
 // Slabs of a request: one per layer, two on the sub-layer grid.
 static int request_slabs(const rt_request *r) { return r->T_center ? 2 * r->n_layers : r->n_layers; }
 
+// Where AUTO may take the deep kernel (prefer_deep), FP64 takes the stream kernel on
+// shorter or more columns, whose segments in one workgroup are done before the deep path's
+// launches (us, deep | stream, columns x slabs x lanes: 16 x 60 x 30: 34 | 29, 16 x 130 x 30:
+// 38 | 46, 64 x 100 x 30: 43 | 41, 128 x 200 x 30: 89 | 60, 16 x 40 x 64: 35 | 31, 16 x 60
+// x 64: 35 | 44; in rt_deep.hip's seven launches 32 x 100 x 100: 68 | 61, 32 x 200 x 100: 85 |
+// 108, 16 x 200 x 300: 154 | 118).  In mixed precision the paths round differently (the
+// deep one keeps 1 - t of thin layers), so AUTO's results stay the deep path's.
+static bool deep_beats_stream(const rt_handle *h, const rt_request *r, int N)
+{
+    if (r->precision != RT_FP64) return true;
+    const long long lanes = (long long)r->n_cols * h->NBG;
+    if (h->NBG > 64) return N >= 130 && lanes <= 3200;
+    return 4ll * r->n_cols <= h->dev.n_cu && N >= (h->NBG > 32 ? 56 : 112);
+}
+
 static rtk::Geometry request_geometry(const rt_handle *h, const rt_request *r)
 {
     const int N = request_slabs(r);
+    rtk::Geometry deep{};
     if (r->kernel == RT_KERNEL_DEEP ||
-        (r->kernel == RT_KERNEL_AUTO && r->cols_per_block == 0 && prefer_deep(h, r->n_cols, N)))
-        return rtk::deep_geometry(r->n_cols, N, h->NBG, h->dev);
+        (r->kernel == RT_KERNEL_AUTO && r->cols_per_block == 0 && prefer_deep(h, r->n_cols, N))) {
+        deep = rtk::deep_geometry(r->n_cols, N, h->NBG, h->dev);
+        if (r->kernel == RT_KERNEL_DEEP || deep.threads == 0 || deep_beats_stream(h, r, N)) return deep;
+    }
     const int kernel = r->kernel == RT_KERNEL_LANE ? rtk::KERNEL_LANE : rtk::KERNEL_LAYER;
     const rtk::Geometry g = rtk::solve_geometry(r->n_cols, N, h->NBG, r->cols_per_block, kernel,
                                                 r->precision, h->dev, h->NG);
-    if (kernel == rtk::KERNEL_LANE || r->cols_per_block != 0 || g.threads == 0) return g;
+    if (kernel == rtk::KERNEL_LANE || r->cols_per_block != 0 || (g.threads == 0 && deep.threads == 0)) return g;
     rtk::Geometry gs = rtk::stream_geometry(r->n_cols, N, h->NBG, h->NG, r->precision == RT_MIXED, h->dev);
-    if (gs.threads == 0) return g;
-    gs.scratch = g.scratch;   // the layer kernel's reservation, which holds the same records
+    if (gs.threads == 0) return deep.threads > 0 ? deep : g;
+    // the layer kernel's reservation, which holds the same records, or the work buffer of
+    // AUTO at this size, as rt_work_bytes states it
+    gs.scratch = std::max(gs.scratch, deep.threads > 0 ? deep.scratch : g.scratch);
     return gs;
 }
 
-static hipError_t launch(const rtk::SolveArgs &a, const rtk::Geometry &g, int precision, hipStream_t s)
+static hipError_t launch(const rtk::SolveArgs &a, const rtk::Geometry &g, int precision,
+                         const rtk::DeviceLimits &dev, hipStream_t s)
 {
     switch (g.kernel) {
-    case rtk::KERNEL_DEEP: return rtk::launch_deep(a, g, precision, s);
+    case rtk::KERNEL_DEEP:
+        if (rtk::cascade_fits(g, a.C, a.N, a.NB, a.NG, a.sub != 0, dev))
+            return rtk::launch_cascade(a, g, precision, s);
+        return rtk::launch_deep(a, g, precision, s);
     case rtk::KERNEL_STREAM: return rtk::launch_stream(a, g, precision, s);
     default: return rtk::launch_solve(a, g, precision, s);
     }
@@ -711,7 +735,7 @@ extern "C" rt_status rt_solve_fluxes(rt_handle *h, const rt_request *r, void *st
         h->scratch_bytes = need;
     }
     rtk::SolveArgs a = make_args(h, r, h->d_scratch);
-    hipError_t e = launch(a, g, r->precision, (hipStream_t)stream);
+    hipError_t e = launch(a, g, r->precision, h->dev, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(h, e, "solve launch");
     return RT_OK;
 }
@@ -729,7 +753,7 @@ extern "C" rt_status rt_solve_fluxes_noalloc(rt_handle *h, const rt_request *r, 
     // the kernels write every word of the work buffer they read later, so it
     // needs no clearing between calls
     rtk::SolveArgs a = make_args(h, r, h->static_ws);
-    hipError_t e = launch(a, g, r->precision, (hipStream_t)stream);
+    hipError_t e = launch(a, g, r->precision, h->dev, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(h, e, "solve launch");
     return RT_OK;
 }
@@ -1015,7 +1039,7 @@ static void pump(rt_handle *h)
             rtk::SolveArgs a = make_args(h, &j.req, (double *)(h->arena.base + off));
             a.status = b.d_status;
             hipError_t e = hipMemsetAsync(b.d_status, 0, sizeof(uint32_t), s);
-            if (e == hipSuccess) e = rtk::launch_deep(a, j.g, prec, s);
+            if (e == hipSuccess) e = launch(a, j.g, prec, h->dev, s);
             if (e == hipSuccess)
                 e = hipMemcpyAsync(b.h_status, b.d_status, sizeof(uint32_t), hipMemcpyDeviceToHost, s);
             if (e == hipSuccess) e = hipEventRecord(b.done, s);
@@ -1115,6 +1139,7 @@ extern "C" rt_status rt_submit(rt_handle *h, const rt_request *r, uint64_t *tick
     // the others (deep and lane kernels, FP32 inputs) run as batched launches
     bool worker = false;
     if (h->cfg.serve_mode == RT_SERVE_PERSISTENT && !h->wbroken &&
+        !(r->kernel == RT_KERNEL_AUTO && r->cols_per_block == 0 && prefer_deep(h, r->n_cols, request_slabs(r))) &&
         (j.g.kernel == rtk::KERNEL_LAYER || j.g.kernel == rtk::KERNEL_STREAM) &&
         r->input_dtype == RT_F64) {
         const rtk::Geometry gw = rtk::worker_geometry(r->n_cols, request_slabs(r), h->NBG, r->precision,

@@ -798,4 +798,6 @@ hipError_t launch_deep(const SolveArgs &a, const Geometry &g, int precision, hip
     return hipGetLastError();
 }
 
+int deep_items_rows(int Ls, int NB, int NBR, bool mixed) { return items_threads(Ls, NB, NBR, mixed) / NB; }
+
 }  // namespace rtk

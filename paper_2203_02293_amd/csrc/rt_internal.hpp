@@ -138,6 +138,12 @@ hipError_t prepare_stream_kernels(const DeviceLimits &dev);
 Geometry deep_geometry(int C, int N, int NB, const DeviceLimits &dev);
 hipError_t launch_deep(const SolveArgs &a, const Geometry &g, int precision, hipStream_t s);
 hipError_t prepare_deep_kernels(const DeviceLimits &dev);
+// Levels per chunk of its items kernel, and partial sums of the optical depth above a segment.
+int deep_items_rows(int Ls, int NB, int NBR, bool mixed);
+// The deep path of columns of up to 64 lanes, where it fits a deep geometry and its work buffer.
+bool cascade_fits(const Geometry &g, int C, int N, int NB, int NG, bool sub, const DeviceLimits &dev);
+hipError_t launch_cascade(const SolveArgs &a, const Geometry &g, int precision, hipStream_t s);
+hipError_t prepare_cascade_kernels(const DeviceLimits &dev);
 // Several requests with the same kernel, tile, bins and precision in one launch:
 // device arrays d_reqs[n] (K, PC, CH, L filled in) and d_first[n] (first
 // workgroup of each).

@@ -135,6 +135,77 @@ __device__ __forceinline__ R bin_radiance(const R *re, double Td, float fb, floa
     return R(kPref) * T2 * T2 * I;
 }
 
+// The elimination's map of (c, eps = 1 - c, d) over a run of layers.  With den = (1 - r)
+// + r eps, elim_step (rt_physics.hpp) takes w (1, eps, c, d) to w' (1, eps', c', d'), w' =
+// w den, linearly in (w, e, c, d) = w (1, eps, c, d):
+//   w' = (1-r) w + r e,  e' = A (1-r+t) w + (r (1-r) + t^2) e,
+//   c' = r w' + t^2 c,   d' = S_dn w' + t (d + S_up c),
+// so a run is the product of its layers' matrices.  The columns of w, e and c are
+// non-negative: no digit is lost.  m: w and e from (e, w); c from (c, e, w); d from (d,
+// c, e, w) at the top.
+struct StateMap {
+    double m[11] = {0, 1, 1, 0, 1, 0, 0, 1, 0, 0, 0};
+    __device__ __forceinline__ void step(double t, double r, double omr, double A, double Sup, double Sdn)
+    {
+        const double tt = t * t, a1 = A * (omr + t), a2 = fma(r, omr, tt);
+        const double we = fma(omr, m[0], r * m[2]), ww = fma(omr, m[1], r * m[3]);
+        m[2] = fma(a1, m[0], a2 * m[2]);
+        m[3] = fma(a1, m[1], a2 * m[3]);
+        m[0] = we;
+        m[1] = ww;
+        m[7] *= t;
+        m[8] = t * fma(Sup, m[4], m[8]);
+        m[9] = fma(Sdn, we, t * fma(Sup, m[5], m[9]));
+        m[10] = fma(Sdn, ww, t * fma(Sup, m[6], m[10]));
+        m[4] *= tt;
+        m[5] = fma(r, we, tt * m[5]);
+        m[6] = fma(r, ww, tt * m[6]);
+    }
+    // by a power of two, so that w stays in range (every few layers: w' >= w (1 - r))
+    __device__ __forceinline__ void rescale()
+    {
+        const int e = -ilogb_pos(m[0] + m[1]);
+#pragma unroll
+        for (int v = 0; v < 11; ++v) m[v] = ldexp(m[v], e);
+    }
+    __device__ __forceinline__ ElimState state() const { return {m[0], m[1], m[2]}; }
+    __device__ __forceinline__ void set_state(const ElimState &s) { m[0] = s.c, m[1] = s.eps, m[2] = s.d; }
+    // the map to a given state
+    __device__ __forceinline__ static StateMap constant(const ElimState &s)
+    {
+        return {{0, 1, 0, s.eps, 0, 0, s.c, 0, 0, 0, s.d}};
+    }
+    __device__ __forceinline__ static int ilogb_pos(double x) { return x > 0.0 ? __builtin_amdgcn_frexp_exp(x) : 0; }
+    __device__ __forceinline__ void apply(ElimState &s) const
+    {
+        const double i = 1.0 / fma(m[0], s.eps, m[1]);
+        const double c = fma(m[4], s.c, fma(m[5], s.eps, m[6]));
+        const double d = fma(m[7], s.d, fma(m[8], s.c, fma(m[9], s.eps, m[10])));
+        s.eps = fma(m[2], s.eps, m[3]) * i;
+        s.c = c * i;
+        s.d = d * i;
+    }
+};
+
+// t, r and the absorptance A of a layer, t + r + A = 1, in two doubles: the two that are
+// not the largest, which is 1 minus them (at least 1/3, so to three units of roundoff);
+// which one it is in their lowest bits.
+__device__ __forceinline__ double2 pack_tra(double t, double r, double A)
+{
+    const bool tl = t >= r && t >= A, al = !tl && A >= r;   // the largest: t, A, else r
+    const double p = tl ? r : t, q = al ? r : A;
+    return make_double2(__hiloint2double(__double2hiint(p), (__double2loint(p) & ~1) | (tl ? 1 : 0)),
+                        __hiloint2double(__double2hiint(q), (__double2loint(q) & ~1) | (al ? 1 : 0)));
+}
+__device__ __forceinline__ void unpack_tra(double2 v, double &t, double &r, double &A)
+{
+    const bool tl = __double2loint(v.x) & 1, al = __double2loint(v.y) & 1;
+    const double big = (1.0 - v.x) - v.y;
+    t = tl ? big : v.x;
+    A = al ? big : v.y;
+    r = tl ? v.x : (al ? v.y : big);
+}
+
 // Workgroup of request r with first[r] <= g < first[r+1] (batched launches).
 __device__ __forceinline__ int batch_request(const int *first, int n, int g)
 {

@@ -102,3 +102,53 @@ def test_deep_request_errors(rt, torch):
     assert s.kernel_for(inp, out) == DEEP
     assert s.kernel_for(inp, out, kernel=rt.RT_KERNEL_LAYER) == rt.RT_KERNEL_LAYER
     s.close()
+
+
+# segments split into parts of six layers: a last segment of one layer, parts of every
+# length, groups of 8 to 64 lanes, the most parts of a workgroup and one more, and what the
+# parts do not take (fewer than six layers)
+PARTS = [(1, 5, 30), (1, 8, 1), (1, 9, 30), (3, 41, 9), (2, 49, 33), (1, 47, 64), (2, 52, 16), (48, 910, 5),
+         (40, 600, 40), (40, 700, 40)]
+
+
+@pytest.mark.parametrize("C,N,NB", PARTS)
+def test_deep_parts(rt, torch, C, N, NB):
+    print(f"\n[deep] {C}x{N}x{NB}", flush=True)
+    w = deep_work(C, N, NB, seed=570 + NB, cloud="fraction", cloud_fraction=0.5)
+    ref = O.solve(w, per_bin=True, extended=True)
+    for prec, tol in ((rt.RT_FP64, FP64_TOL), (rt.RT_MIXED, MIXED_TOL)):
+        out = gpu_solve(rt, torch, w, prec, per_bin=True, kernel=DEEP)
+        e = assert_close(out, ref, w["p_iface"], tol, floor=FLOOR[prec], floor_bin=FLOOR_BIN[prec])
+        print(f"  precision={prec} errors={e}", flush=True)
+        np.testing.assert_array_equal(out["flags"], ref["flags"])
+
+
+# an even and an odd number of slabs per segment (which the parts leave to whole segments)
+@pytest.mark.parametrize("C,layers", [(2, 23), (30, 95)])
+def test_deep_parts_sublayer_grid(rt, torch, C, layers):
+    w = synth.make_sublayer(synth.Spec(name="s", g_level=3, n_layers=layers, n_bins=7, cloud="night", seed=581),
+                            n_cols=C)
+    ref = O.solve_sublayer(w, per_bin=True, extended=True)
+    for prec, tol in ((rt.RT_FP64, FP64_TOL), (rt.RT_MIXED, MIXED_TOL)):
+        out = gpu_solve(rt, torch, w, prec, per_bin=True, kernel=DEEP)
+        assert_close(out, ref, w["p_iface"], tol, floor=FLOOR[prec], floor_bin=FLOOR_BIN[prec])
+        np.testing.assert_array_equal(out["flags"], ref["flags"])
+
+
+def test_deep_parts_gauss_points(rt, torch):
+    w = synth.make_kdist(synth.Spec(name="k", g_level=3, n_layers=61, n_bins=5, cloud="night", seed=591),
+                         n_cols=3, n_gauss=4)
+    ref = O.solve(w, per_bin=True, extended=True)
+    for prec, tol in ((rt.RT_FP64, FP64_TOL), (rt.RT_MIXED, MIXED_TOL)):
+        out = gpu_solve(rt, torch, w, prec, per_bin=True, kernel=DEEP)
+        assert_close(out, ref, w["p_iface"], tol, floor=FLOOR[prec], floor_bin=FLOOR_BIN[prec])
+
+
+# AUTO on both sides of its lines between the deep and the stream kernel, in FP64
+@pytest.mark.parametrize("C,N,NB", [(64, 111, 30), (64, 112, 30), (65, 112, 30), (3, 55, 40), (3, 56, 40), (32, 130, 100)])
+def test_auto_deep_or_stream(rt, torch, C, N, NB):
+    w = deep_work(C, N, NB, seed=595)
+    ref = gpu_solve(rt, torch, w, rt.RT_FP64, kernel=DEEP)
+    out = gpu_solve(rt, torch, w, rt.RT_FP64, kernel=0, cols_per_block=0)
+    assert_close(out, ref, w["p_iface"], FP64_TOL, floor=FLOOR[0], floor_bin=FLOOR_BIN[0])
+    np.testing.assert_array_equal(out["flags"], ref["flags"])
