@@ -460,17 +460,18 @@ static int request_slabs(const rt_request *r) { return r->T_center ? 2 * r->n_la
 
 // Where AUTO may take the deep kernel (prefer_deep), FP64 takes the stream kernel on
 // shorter or more columns, whose segments in one workgroup are done before the deep path's
-// launches (us, deep | stream, columns x slabs x lanes: 16 x 60 x 30: 34 | 29, 16 x 130 x 30:
-// 38 | 46, 64 x 100 x 30: 43 | 41, 128 x 200 x 30: 89 | 60, 16 x 40 x 64: 35 | 31, 16 x 60
-// x 64: 35 | 44; in rt_deep.hip's seven launches 32 x 100 x 100: 68 | 61, 32 x 200 x 100: 85 |
-// 108, 16 x 200 x 300: 154 | 118).  In mixed precision the paths round differently (the
-// deep one keeps 1 - t of thin layers), so AUTO's results stay the deep path's.
+// launches (us, deep | stream, columns x slabs x lanes: 16 x 80 x 30: 36 | 32, 16 x 100 x 30:
+// 36 | 40, 128 x 200 x 30: 89 | 60, 16 x 40 x 64: 35 | 31, 16 x 60 x 64: 35 | 44; in
+// rt_deep.hip's seven launches 16 x 80 x 100: 53 | 54, 16 x 100 x 100: 49 | 60, 4 x 100 x
+// 300: 74 | 63, 4 x 130 x 300: 75 | 81, 16 x 200 x 300: 154 | 118).  In mixed precision the
+// paths round differently (the deep one keeps 1 - t of thin layers), so AUTO's results stay
+// the deep path's.
 static bool deep_beats_stream(const rt_handle *h, const rt_request *r, int N)
 {
     if (r->precision != RT_FP64) return true;
     const long long lanes = (long long)r->n_cols * h->NBG;
-    if (h->NBG > 64) return N >= 130 && lanes <= 3200;
-    return 4ll * r->n_cols <= h->dev.n_cu && N >= (h->NBG > 32 ? 56 : 112);
+    if (h->NBG > 64) return N >= 64 + h->NBG / 4 && lanes <= 3200;
+    return 4ll * r->n_cols <= h->dev.n_cu && N >= (h->NBG > 32 ? 48 : 88);
 }
 
 static rtk::Geometry request_geometry(const rt_handle *h, const rt_request *r)

@@ -145,7 +145,7 @@ def test_deep_parts_gauss_points(rt, torch):
 
 
 # AUTO on both sides of its lines between the deep and the stream kernel, in FP64
-@pytest.mark.parametrize("C,N,NB", [(64, 111, 30), (64, 112, 30), (65, 112, 30), (3, 55, 40), (3, 56, 40), (32, 130, 100)])
+@pytest.mark.parametrize("C,N,NB", [(64, 87, 30), (64, 88, 30), (65, 88, 30), (3, 47, 40), (3, 48, 40), (32, 89, 100)])
 def test_auto_deep_or_stream(rt, torch, C, N, NB):
     w = deep_work(C, N, NB, seed=595)
     ref = gpu_solve(rt, torch, w, rt.RT_FP64, kernel=DEEP)
