@@ -66,10 +66,11 @@ def algorithmic_bytes(C: int, N: int, NB: int) -> int:
 
 
 def kernel_source_hash() -> str:
-    """Hash of the sources the lane and layer kernels are compiled from."""
+    """Hash of the sources the solve kernels are compiled from."""
     h = hashlib.sha256()
     csrc = ROOT / "paper_2203_02293_amd" / "csrc"
-    for name in ("rt_internal.hpp", "rt_kernels.hip", "rt_math.hpp", "rt_physics.hpp", "rt_wave.hpp"):
+    for name in ("rt_internal.hpp", "rt_kernels.hip", "rt_lanes.hpp", "rt_math.hpp", "rt_physics.hpp",
+                 "rt_planck.hpp", "rt_stream.hip", "rt_wave.hpp"):
         h.update((csrc / name).read_bytes())
     return h.hexdigest()[:16]
 

@@ -607,41 +607,49 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
 }
 
 // Columns of more than 64 lanes, after k_solve_stream: a workgroup adds its column's
-// slices, in order.
+// slices, in order, each sum once and eight slices' loads at a time (added at each use, one
+// load after the other, 10242 x 80 x 300 took 169 us here and 2562 x 40 x 600 lanes 44).
 __device__ __forceinline__ void solve_columns(ArgsK ap, const int c)
 {
+    extern __shared__ double s_sums[];   // [3 (N + 1)]
     __shared__ uint32_t s_flag;
     auto args = [&]() -> const SolveArgs & { return *(const SolveArgs *)ap; };
-    const int NB = args().NB, NG = args().NG, C = args().C, N = args().N, tid = threadIdx.x;
+    const int NG = args().NG, N = args().N, tid = threadIdx.x;
     const StreamShape sh = StreamShape::unpack(args().CH, args().L);
+    const int NB = args().NB;
     auto slice = [&](int w) -> const double * {
         return reinterpret_cast<const double *>(record_block(args().scratch, N, NB, c, w * sh.NBs));
     };
-    auto value = [&](int w, int t) -> double { return slice(w)[t]; };
-    if (tid == 0) {
-        uint32_t f = 0u;
-        for (int w = 0; w < sh.NBw; ++w) f |= (uint32_t)value(w, 3 * (N + 1));
-        s_flag = f;
+    const int n = 3 * (N + 1);
+    if (tid == 0) s_flag = 0u;
+    __syncthreads();
+    if (tid < sh.NBw) atomicOr(&s_flag, (uint32_t)slice(tid)[n]);
+    for (int t = tid; t < n; t += blockDim.x) {
+        double s = 0.0;
+        for (int w = 0; w < sh.NBw; w += 8) {
+            double v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = slice(min(w + k, sh.NBw - 1))[t];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) s += w + k < sh.NBw ? v[k] : 0.0;
+        }
+        s_sums[t] = s;
     }
     __syncthreads();
     if (NG > 1 && args().F_up_toa_bin) {   // the spectrum: weighted sums over each bin's points
         for (int r = tid; r < sh.NBR; r += blockDim.x) {
             double s = 0.0;
             for (int g = 0; g < NG; ++g) {
-                const int l = r * NG + g, w = small_div(l, sh.NBs), n = min(sh.NBs, NB - w * sh.NBs);
-                s += args().wg[g] * slice(w)[(2 * N - 1) * n * 2 + l - w * sh.NBs];
+                const int l = r * NG + g, w = small_div(l, sh.NBs), lanes = min(sh.NBs, NB - w * sh.NBs);
+                s += args().wg[g] * slice(w)[(2 * N - 1) * lanes * 2 + l - w * sh.NBs];
             }
             args().F_up_toa_bin[(long long)c * sh.NBR + r] = s;
         }
     }
-    write_columns(ap, c, 1, &s_flag, [&](int l, int v, int) {
-        double s = 0.0;
-        for (int w = 0; w < sh.NBw; ++w) s += value(w, 3 * l + v);
-        return s;
-    });
+    write_columns(ap, c, 1, &s_flag, [&](int l, int v, int) { return s_sums[3 * l + v]; });
 }
 
-constexpr int kColumnThreads = 64;   // of k_stream_columns
+constexpr int kColumnThreads = 128;   // of k_stream_columns
 
 // Workgroups go to the eight XCDs in turn; workgroup g of a grid of 8 n takes tile
 // (g % 8) n + g / 8, so each XCD's L2 sees a run of neighbouring columns (slices of a
@@ -777,7 +785,7 @@ hipError_t launch_stream(const SolveArgs &a, const Geometry &g, int precision, h
         hipLaunchKernelGGL((k_solve_stream<decltype(mixed)::value, decltype(in32)::value, decltype(seg)::value>),
                            dim3(g.blocks), dim3(g.threads), g.lds, s, b);
     });
-    if (a.NB > 64) hipLaunchKernelGGL(k_stream_columns, dim3(a.C), dim3(kColumnThreads), 0, s, b);
+    if (a.NB > 64) hipLaunchKernelGGL(k_stream_columns, dim3(a.C), dim3(kColumnThreads), 3 * (a.N + 1) * sizeof(double), s, b);
     return hipGetLastError();
 }
 
@@ -789,7 +797,7 @@ hipError_t launch_stream_batch(const SolveArgs *d_reqs, const int *d_first, int 
                            dim3(total_blocks), dim3(g.threads), g.lds, s, d_reqs, d_first, n);
     });
     if (NB > 64)
-        hipLaunchKernelGGL(k_stream_columns_batch, dim3(total_blocks), dim3(kColumnThreads), 0, s, d_reqs, d_first, n);
+        hipLaunchKernelGGL(k_stream_columns_batch, dim3(total_blocks), dim3(kColumnThreads), g.lds, s, d_reqs, d_first, n);
     return hipGetLastError();
 }
 
@@ -805,6 +813,8 @@ hipError_t prepare_stream_kernels(const DeviceLimits &dev)
                 if (e == hipSuccess)
                     e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dev.lds);
         });
+    for (const void *f : {reinterpret_cast<const void *>(&k_stream_columns), reinterpret_cast<const void *>(&k_stream_columns_batch)})
+        if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dev.lds - 1024);
     return e != hipSuccess ? e : upload_planck_table();
 }
 
