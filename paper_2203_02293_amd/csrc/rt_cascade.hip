@@ -306,7 +306,7 @@ __global__ void __launch_bounds__(512, 2) k_cascade_items(const SolveArgs a)
         for (int q = 0; q < 8; ++q) tau += k + q < before ? above[q] : 0.0;
     }
     const double iT = rcp(T);
-    if (e0 == 0) s_T[row] = T;
+    if (e0 == 0) s_T[row] = level_value<MIXED>(T);
     R *re = s_edge + row * lo.estride;
     for (int i = 0; i <= NBR; i += 2 * epr) {
         const int e1 = min(i + e0, NBR), e2 = min(i + epr + e0, NBR);

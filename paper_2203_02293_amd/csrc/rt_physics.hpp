@@ -458,7 +458,7 @@ __host__ __device__ __forceinline__ Layer<R> layer_item(double dt, double w, dou
                                                         double Fb_lo, R Blo, R Bup, const Opts &o,
                                                         double inv_eps2, uint32_t &fl)
 {
-    if (!(dt >= 0.0) || !isfinite(dt) || !(w >= 0.0 && w <= 1.0) || !(g > -1.0 && g < 1.0))
+    if (!(dt >= 0.0) || !isfinite(dt) || !(w >= 0.0 && w <= 1.0) || !(fabs(g) < 1.0))
         fl |= F_INVALID;
     const double E = efit_exact(w, g, o, fl);
     bool guard = false;

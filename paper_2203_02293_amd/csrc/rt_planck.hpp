@@ -114,12 +114,11 @@ struct ExpCoef6 {
     static constexpr double coef(int j) { return inv_fact(j + 1); }
 };
 
-// e^-x, x >= 0: x = k ln2 / 32 + r, |r| <= ln2 / 64, from the table's 2^(-j/32), j = k
+// e^-x, 0 <= x <= 800 (from 746 on 0): x = k ln2 / 32 + r, |r| <= ln2 / 64, from the table's 2^(-j/32), j = k
 // mod 32, and the Taylor polynomial of e^-r - 1 (next term below 4e-18).
 __host__ __device__ __forceinline__ double exp_neg(double x, const double *table)
 {
     constexpr double M = 6755399441055744.0;   // 1.5 x 2^52: x + M holds rint(x) in its low bits
-    x = fmin(x, 760.0);
     const double m = fma(x, 32.0 * ExpCfg<double>::LOG2E, M), k = m - M;
     double r = fma(k, -ExpCfg<double>::LN2_HI / 32.0, x);
     r = fma(k, -ExpCfg<double>::LN2_LO / 32.0, r);
@@ -138,8 +137,7 @@ __host__ __device__ __forceinline__ double exp_neg(double x, const double *table
 // wavefront fall on both sides of x = 3, and two calls overlap.  table: 16-byte aligned.
 __host__ __device__ __forceinline__ double planck_lookup(double x, const double *table)
 {
-    const bool in = x < PCfg<double>::XCUT;
-    x = in ? x : 0.0;
+    x = fmin(x, 800.0);   // (and NaN: e^-800 is 0)
     double c;
     const int k = planck_cell(x, c), kc = k < kPlanckCells ? k : kPlanckCells - 1;
     const double t = x - c;
@@ -158,7 +156,7 @@ __host__ __device__ __forceinline__ double planck_lookup(double x, const double 
     }
     s = k >= kPlanckCells ? fma(x, fma(x, x + 3.0, 6.0), 6.0) : s;
     const double f = k < kPlanckSplit ? x * x * x : -exp_neg(x, table);
-    return in ? f * s : -0.0;
+    return f * s;
 }
 
 }  // namespace rtk

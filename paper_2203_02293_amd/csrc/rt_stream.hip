@@ -315,7 +315,7 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
         if (rq >= from && rq < n) {
             if (check && (!(T > 0.0) || !isfinite(T))) atomicOr(&s_flag[rg.kk], (uint32_t)F_INVALID);
             const double iT = rcp(T);
-            if (e0 == 0) s_T[row] = T;
+            if (e0 == 0) s_T[row] = level_value<MIXED>(T);
             if (!MIXED || !narrow) {
             // two at a time (past the last edge: that one again), so that their chains overlap
             R *re = s_edge + row * lo.estride;
