@@ -163,7 +163,7 @@ __host__ __device__ __forceinline__ ItemsLds items_lds(int gw, int waves, int NB
     o.tab = 0;
     o.c2 = mixed ? 0 : kPlanckTable * 8;
     o.temp = 0;
-    o.val = (size_t)gw * kRows * 8;
+    o.val = (size_t)gw * kRows * (mixed ? 16 : 8);
     o.edge = o.val + kRows * kStride * 8;
     o.per_wave = (o.edge + (size_t)gw * kRows * o.estride * (mixed ? 4 : 8) + 15) & ~size_t(15);
     if (o.per_wave < kShared * 64 * 8) o.per_wave = kShared * 64 * 8;
@@ -241,7 +241,8 @@ __global__ void __launch_bounds__(512, 2) k_cascade_items(const SolveArgs a)
     const ItemsLds lo = items_lds(d.gw, W >> 6, NBR, a.CH, MIXED);
     double *s_tab = reinterpret_cast<double *>(lds + lo.tab), *s_c2 = reinterpret_cast<double *>(lds + lo.c2);
     char *regions = lds + lo.total - (W >> 6) * lo.per_wave, *own = regions + wave * lo.per_wave;
-    double *s_T = reinterpret_cast<double *>(own + lo.temp), *s_val = reinterpret_cast<double *>(own + lo.val);
+    LevelValue<MIXED> *s_level = reinterpret_cast<LevelValue<MIXED> *>(own + lo.temp);
+    double *s_val = reinterpret_cast<double *>(own + lo.val);
     R *s_edge = reinterpret_cast<R *>(own + lo.edge);
     const long long l = (long long)c * NB + b;
     const int a0 = me.e1 - kPart;   // slab (from the TOA) of the first step
@@ -306,7 +307,7 @@ __global__ void __launch_bounds__(512, 2) k_cascade_items(const SolveArgs a)
         for (int q = 0; q < 8; ++q) tau += k + q < before ? above[q] : 0.0;
     }
     const double iT = rcp(T);
-    if (e0 == 0) s_T[row] = level_value<MIXED>(T);
+    if (e0 == 0) s_level[row] = LevelValue<MIXED>::of(T);
     R *re = s_edge + row * lo.estride;
     for (int i = 0; i <= NBR; i += 2 * epr) {
         const int e1 = min(i + e0, NBR), e2 = min(i + epr + e0, NBR);
@@ -317,7 +318,7 @@ __global__ void __launch_bounds__(512, 2) k_cascade_items(const SolveArgs a)
     wave_sync();
     auto bin_B = [&](int r) -> R {
         const int rw = gl * kRows + r;
-        return bin_radiance<MIXED, R>(s_edge + rw * lo.estride + bin, s_T[rw], c2fb, c2fa, s_c2 + bin, false);
+        return bin_radiance<MIXED, R>(s_edge + rw * lo.estride + bin, s_level[rw], c2fb, c2fa, s_c2 + bin, false);
     };
 
     double Fb_up = day ? (me.i == 0 ? muF : beam_at<MIXED>(muF, tau, inv_mu)) : 0.0;

@@ -115,35 +115,40 @@ __device__ __forceinline__ double level_T(const SolveArgs &a, bool sub, int l, i
     return base[(long long)(sub ? (l >> 1) : l) * a.C + cc];
 }
 
-// Bin radiance at a level of value Td (level_value) from the edge integrals re[0], re[1] of the
-// bin; c2b, c2a: c2 / lambda at its edges (LDS), fb, fa the same in FP32.  narrow (MIXED):
-// all bins are (planck_narrow), and there are no edge integrals.
+// What the bin radiances take of a level's temperature, worked out once per level: the
+// Planck prefactor; in mixed precision 1 / T as well, for the narrow bins.
+template <bool MIXED>
+struct LevelValue {
+    double prefactor;
+    __device__ __forceinline__ static LevelValue of(double T) { return {kPref * (T * T) * (T * T)}; }
+};
+template <>
+struct LevelValue<true> {
+    double iT;
+    float iTf, prefactor;
+    __device__ __forceinline__ static LevelValue of(double T)
+    {
+        const float Tf = float(T), T2 = Tf * Tf;
+        return {rcp(T), rcp(Tf), float(kPref) * T2 * T2};
+    }
+};
+
+// Bin radiance at a level from the edge integrals re[0], re[1] of the bin; c2b, c2a: c2 /
+// lambda at its edges (LDS), fb, fa the same in FP32.  narrow (MIXED): all bins are
+// (planck_narrow), and there are no edge integrals.
 template <bool MIXED, class R>
-__device__ __forceinline__ R bin_radiance(const R *re, double Td, float fb, float fa, const double *c2, bool narrow)
+__device__ __forceinline__ R bin_radiance(const R *re, const LevelValue<MIXED> &lv, float fb, float fa, const double *c2,
+                                          bool narrow)
 {
     if constexpr (!MIXED) {
-        return Td * planck_combine<R>(re[0], re[1]);
+        return lv.prefactor * planck_combine<R>(re[0], re[1]);
     } else {
-        const R Tr = R(Td), T2 = Tr * Tr;
         R I = R(0);
         if (!narrow) I = planck_combine<R>(re[0], re[1]);
-        const R iT = rcp(Tr);
-        const R xb = fb * iT, xa = fa * iT;
-        if (narrow || planck_narrow(xa, xb)) {
-            const double iTd = rcp(Td);
-            I = planck_gl3(c2[1] * iTd, c2[0] * iTd);
-        }
-        return R(kPref) * T2 * T2 * I;
+        const R xb = fb * lv.iTf, xa = fa * lv.iTf;
+        if (narrow || planck_narrow(xa, xb)) I = planck_gl3(c2[1] * lv.iT, c2[0] * lv.iT);
+        return lv.prefactor * I;
     }
-}
-
-// What bin_radiance takes of a level's temperature: itself (mixed), or in FP64 its Planck
-// prefactor, once per level.
-template <bool MIXED>
-__device__ __forceinline__ double level_value(double T)
-{
-    if constexpr (MIXED) return T;
-    else return kPref * (T * T) * (T * T);
 }
 
 // The elimination's map of (c, eps = 1 - c, d) over a run of layers.  With den = (1 - r)

@@ -69,7 +69,7 @@ struct StreamLds {
     int estride;                         // edge values per row (odd: rows start in different banks)
     size_t per_wave;                     // a wavefront's own region
     size_t edge, val, temp;              // in it: R [gw kChunk][estride]; double [kChunk][kSumStride], twice
-                                         // (the second one in place of the edges); double [gw kChunk]
+                                         // (the second one in place of the edges); LevelValue [gw kChunk]
     size_t tab, c2, sum, top, flag, total;
 };
 // K columns of S segments each on `waves` wavefronts: K S = gw waves
@@ -81,7 +81,7 @@ __host__ __device__ __forceinline__ StreamLds stream_lds(const StreamShape &sh, 
     const size_t rows = (size_t)gw * kChunk, buf = kChunk * kSumStride * 8;
     const size_t e = (rows * o.estride * (mixed ? 4 : 8) + 7) & ~size_t(7);
     o.temp = 0;
-    o.val = rows * 8;
+    o.val = rows * (mixed ? 16 : 8);
     o.edge = o.val + buf;
     o.per_wave = o.edge + (e > buf ? e : buf);
     o.tab = 0;                                                                  // FP64: the Planck table
@@ -164,7 +164,7 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
     char *own = lds + (MIXED ? 0 : kPlanckTable * 8) + (size_t)wave * lo.per_wave;
     R *s_edge = reinterpret_cast<R *>(own + lo.edge);
     double *s_val = reinterpret_cast<double *>(own + lo.val), *s_val2 = reinterpret_cast<double *>(own + lo.edge);
-    double *s_T = reinterpret_cast<double *>(own + lo.temp);
+    LevelValue<MIXED> *s_level = reinterpret_cast<LevelValue<MIXED> *>(own + lo.temp);
     double *s_c2 = reinterpret_cast<double *>(lds + lo.c2) - bin0;
     double *s_sum = reinterpret_cast<double *>(lds + lo.sum);
     double *s_top = reinterpret_cast<double *>(lds + lo.top);
@@ -315,7 +315,7 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
         if (rq >= from && rq < n) {
             if (check && (!(T > 0.0) || !isfinite(T))) atomicOr(&s_flag[rg.kk], (uint32_t)F_INVALID);
             const double iT = rcp(T);
-            if (e0 == 0) s_T[row] = level_value<MIXED>(T);
+            if (e0 == 0) s_level[row] = LevelValue<MIXED>::of(T);
             if (!MIXED || !narrow) {
             // two at a time (past the last edge: that one again), so that their chains overlap
             R *re = s_edge + row * lo.estride;
@@ -331,7 +331,7 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
     };
     auto bin_B = [&](int q) -> R {
         const int rw = gl * kChunk + q;
-        return bin_radiance<MIXED, R>(s_edge + rw * lo.estride + rb, s_T[rw], c2fb, c2fa, s_c2 + bin, narrow);
+        return bin_radiance<MIXED, R>(s_edge + rw * lo.estride + rb, s_level[rw], c2fb, c2fa, s_c2 + bin, narrow);
     };
     // Column sums of n rows of lane values v (LDS, kSumStride apart) into the sums of
     // levels lev(group, row): lane (q, p) = (ln % 8, ln / 8) adds the 8 lanes p of row
