@@ -1055,7 +1055,7 @@ static void pump(rt_handle *h)
             h->running[j.ticket] = slot;
             continue;
         }
-        int blocks = 0;
+        int blocks = 0, layers = 0;
         rtk::Geometry gb = g0;
         for (auto it = h->queued.begin(); it != h->queued.end() && (int)b.jobs.size() < kMaxBatch;) {
             // one launch shape per batch: same kernel, precision, input storage and
@@ -1083,6 +1083,7 @@ static void pump(rt_handle *h)
             a.L = j.g.lanes;
             a.status = b.d_status + b.jobs.size();
             gb.lds = std::max(gb.lds, j.g.lds);
+            layers = std::max(layers, a.N);
             b.h_args[b.jobs.size()] = a;
             b.h_first[b.jobs.size()] = blocks;
             blocks += j.g.blocks;
@@ -1098,7 +1099,7 @@ static void pump(rt_handle *h)
         if (e == hipSuccess) e = hipMemsetAsync(b.d_status, 0, sizeof(uint32_t) * n, s);
         if (e == hipSuccess)
             e = gb.kernel == rtk::KERNEL_STREAM
-                    ? rtk::launch_stream_batch(b.d_args, b.d_first, n, blocks, gb, h->NBG, prec, in32, s)
+                    ? rtk::launch_stream_batch(b.d_args, b.d_first, n, blocks, layers, gb, h->NBG, prec, in32, s)
                     : rtk::launch_solve_batch(b.d_args, b.d_first, n, blocks, gb, prec, in32, s);
         if (e == hipSuccess)
             e = hipMemcpyAsync(b.h_status, b.d_status, sizeof(uint32_t) * n, hipMemcpyDeviceToHost, s);

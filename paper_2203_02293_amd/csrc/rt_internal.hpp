@@ -130,8 +130,9 @@ hipError_t launch_solve(const SolveArgs &a, const Geometry &g, int precision, hi
 // Wavefront-per-lanes solve (threads = 0: the shape does not fit it).
 Geometry stream_geometry(int C, int N, int NB, int NG, bool mixed, const DeviceLimits &dev);
 hipError_t launch_stream(const SolveArgs &a, const Geometry &g, int precision, hipStream_t s);
+// (layers: the most slabs of a request)
 hipError_t launch_stream_batch(const SolveArgs *d_reqs, const int *d_first, int n, int total_blocks,
-                               const Geometry &g, int NB, int precision, int in_f32, hipStream_t s);
+                               int layers, const Geometry &g, int NB, int precision, int in_f32, hipStream_t s);
 hipError_t prepare_stream_kernels(const DeviceLimits &dev);
 // Layer-parallel path for deep columns (several launches on stream s): K =
 // segments per column, PC = slabs per segment; scratch sized for it.

@@ -650,6 +650,8 @@ __device__ __forceinline__ void solve_columns(ArgsK ap, const int c)
 }
 
 constexpr int kColumnThreads = 128;   // of k_stream_columns
+constexpr int kColumnStaticLds = 1024;   // more than its static LDS
+size_t columns_lds(int N) { return 3 * (size_t)(N + 1) * sizeof(double); }
 
 // Workgroups go to the eight XCDs in turn; workgroup g of a grid of 8 n takes tile
 // (g % 8) n + g / 8, so each XCD's L2 sees a run of neighbouring columns (slices of a
@@ -687,12 +689,13 @@ k_solve_stream_batch(const SolveArgs *__restrict__ reqs, const int *__restrict__
     if (has_tile(reqs[r], tile)) solve_tile_stream<MIXED, IN32, SEG>((ArgsK)(reqs + r), tile);
 }
 
-// first: of k_solve_stream_batch; one workgroup per workgroup of that launch, the
-// first ones of a request take its columns
+// first: of k_solve_stream_batch, whose launch has NBw workgroups or more per column (one
+// handle's requests all have the same lanes per column): request r's columns start at
+// workgroup ceil(first[r] / NBw), and the next one's start after all of them.
 __global__ void __launch_bounds__(kColumnThreads)
-k_stream_columns_batch(const SolveArgs *__restrict__ reqs, const int *__restrict__ first, int n)
+k_stream_columns_batch(const SolveArgs *__restrict__ reqs, const int *__restrict__ first, int n, int NBw)
 {
-    const int r = batch_request(first, n, blockIdx.x), c = blockIdx.x - first[r];
+    const int r = batch_request(first, n, blockIdx.x * NBw), c = blockIdx.x - (first[r] + NBw - 1) / NBw;
     if (c < reqs[r].C) solve_columns((ArgsK)(reqs + r), c);
 }
 
@@ -727,7 +730,7 @@ static Geometry stream_shape(int C, int N, int NB, int NG, int S, bool direct, b
     if ((long long)C * NB >= (1ll << 28) || (S > 1 && (long long)C * NB * N >= (1ll << 27))) return g;
     const StreamShape sh = stream_sizes(N, NB, NG, S);
     g.lds = stream_lds(sh, N, NB, NG, K, ll.gw, waves, mixed).total;
-    if (g.lds > dev.lds) return g;
+    if (g.lds > dev.lds || (NB > 64 && columns_lds(N) > dev.lds - kColumnStaticLds)) return g;
     g.kernel = KERNEL_STREAM;
     g.K = K;
     g.PC = S;
@@ -785,19 +788,22 @@ hipError_t launch_stream(const SolveArgs &a, const Geometry &g, int precision, h
         hipLaunchKernelGGL((k_solve_stream<decltype(mixed)::value, decltype(in32)::value, decltype(seg)::value>),
                            dim3(g.blocks), dim3(g.threads), g.lds, s, b);
     });
-    if (a.NB > 64) hipLaunchKernelGGL(k_stream_columns, dim3(a.C), dim3(kColumnThreads), 3 * (a.N + 1) * sizeof(double), s, b);
+    if (a.NB > 64) hipLaunchKernelGGL(k_stream_columns, dim3(a.C), dim3(kColumnThreads), columns_lds(a.N), s, b);
     return hipGetLastError();
 }
 
 hipError_t launch_stream_batch(const SolveArgs *d_reqs, const int *d_first, int n, int total_blocks,
-                               const Geometry &g, int NB, int precision, int in_f32, hipStream_t s)
+                               int layers, const Geometry &g, int NB, int precision, int in_f32, hipStream_t s)
 {
     with_kernel(precision, in_f32, g.PC > 1, [&](auto mixed, auto in32, auto seg) {
         hipLaunchKernelGGL((k_solve_stream_batch<decltype(mixed)::value, decltype(in32)::value, decltype(seg)::value>),
                            dim3(total_blocks), dim3(g.threads), g.lds, s, d_reqs, d_first, n);
     });
-    if (NB > 64)
-        hipLaunchKernelGGL(k_stream_columns_batch, dim3(total_blocks), dim3(kColumnThreads), g.lds, s, d_reqs, d_first, n);
+    if (NB > 64) {
+        const int NBw = lane_layout(NB).NBw;
+        hipLaunchKernelGGL(k_stream_columns_batch, dim3((total_blocks + NBw - 1) / NBw), dim3(kColumnThreads),
+                           columns_lds(layers), s, d_reqs, d_first, n, NBw);
+    }
     return hipGetLastError();
 }
 
@@ -814,7 +820,7 @@ hipError_t prepare_stream_kernels(const DeviceLimits &dev)
                     e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dev.lds);
         });
     for (const void *f : {reinterpret_cast<const void *>(&k_stream_columns), reinterpret_cast<const void *>(&k_stream_columns_batch)})
-        if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dev.lds - 1024);
+        if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dev.lds - kColumnStaticLds);
     return e != hipSuccess ? e : upload_planck_table();
 }
 

@@ -244,7 +244,7 @@ extern "C" long long emu_deep_scratch(int C, int N, int NB, int ncu, int lds)
 LOCKSTEP = [("auto step = [&](int q, int k) {", "emu_lanes_sync(NBp);"),   # padding lanes: the same records again
             ("auto edges = [&](double T, int from, int n, bool check) {", "emu_wave_sync();"),   # rows read before
             ("constexpr int RD = MIXED ? 4 : 8;", "emu_wave_sync();")]         # rows in place of the edges
-BATCH = ("launch_stream_batch(a.data(), first.data(), n, blocks, gb, a[0].NB, mixed ? 1 : 0, a[0].in_f32, nullptr)")
+BATCH = ("launch_stream_batch(a.data(), first.data(), n, blocks, layers, gb, a[0].NB, mixed ? 1 : 0, a[0].in_f32, nullptr)")
 
 
 def _transform(s: str) -> str:

@@ -72,6 +72,20 @@ def test_stream_batch_equals_single(NB, mixed):
                 np.testing.assert_array_equal(out[k], one[k], err_msg=k)
 
 
+@pytest.mark.parametrize("mixed", [False, True], ids=["fp64", "mixed"])
+def test_served_wide_columns_launch_within_lds(mixed):
+    """A served request of wide columns launches at every layer count: neither of its two
+    kernels asks for more LDS than it is set up for, also where the solve's fills it."""
+    full = 0
+    for C, NB in ((64, 100), (129, 100), (129, 300), (1, 65), (700, 768)):
+        for N in (*range(1, 4096, 17), *range(3800, 4097)):
+            g = run.stream_geometry(C, N, NB, mixed=mixed)
+            full += g["lds"] > run.LDS - 1024
+            if g["threads"]:
+                assert run.batch_launches(C, N, NB, mixed), (C, N, NB, g)
+    assert full
+
+
 # (columns, layers, lanes, compute units): parts of 6 slabs, ragged last segments and parts, 8 to 64
 # lanes, several wavefronts per segment
 CASCADE = [(1, 300, 6, 4), (3, 77, 7, 4), (2, 61, 30, 8), (1, 41, 64, 8), (5, 19, 9, 2), (2, 130, 33, 4)]
