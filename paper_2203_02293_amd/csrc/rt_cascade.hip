@@ -356,8 +356,9 @@ __global__ void __launch_bounds__(512, 2) k_cascade_items(const SolveArgs a)
             x = pack_mixed(Ly.t, Ly.omt, Ly.r, Ly.omr, Ly.A);
             unpack_mixed(x, t, r, omr, A);
         } else {
-            t = Ly.t, r = Ly.r, A = Ly.A, omr = t + A;
-            x = pack_tra(t, r, A);
+            t = Ly.t, r = Ly.r, A = Ly.A, omr = Ly.omr;
+            const StoredLayer v = store_layer(t, r, A);
+            x = make_double2(v.p, v.q);
         }
         // upward emission of the part with this layer below it
         const double w = map.m[0] + map.m[1], e = map.m[2] + map.m[3], D = map.m[9] + map.m[10];
@@ -626,8 +627,8 @@ __global__ void __launch_bounds__(512) k_cascade_back(const SolveArgs a)
             Sup = double(__int_as_float(__double2loint(y[q].x)));
             Sdn = double(__int_as_float(__double2hiint(y[q].x)));
         } else {
-            unpack_tra(x[q], t, r, A);
-            omr = t + A, Sup = y[q].x, Sdn = y[q].y;
+            load_layer({x[q].x, x[q].y}, t, r, omr, A);
+            Sup = y[q].x, Sdn = y[q].y;
         }
         ElimState nx = st;
         const BackRec rec = elim_step(nx, t, r, omr, A, Sup, Sdn);

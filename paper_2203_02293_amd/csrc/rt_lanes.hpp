@@ -203,25 +203,6 @@ struct StateMap {
     }
 };
 
-// t, r and the absorptance A of a layer, t + r + A = 1, in two doubles: the two that are
-// not the largest, which is 1 minus them (at least 1/3, so to three units of roundoff);
-// which one it is in their lowest bits.
-__device__ __forceinline__ double2 pack_tra(double t, double r, double A)
-{
-    const bool tl = t >= r && t >= A, al = !tl && A >= r;   // the largest: t, A, else r
-    const double p = tl ? r : t, q = al ? r : A;
-    return make_double2(__hiloint2double(__double2hiint(p), (__double2loint(p) & ~1) | (tl ? 1 : 0)),
-                        __hiloint2double(__double2hiint(q), (__double2loint(q) & ~1) | (al ? 1 : 0)));
-}
-__device__ __forceinline__ void unpack_tra(double2 v, double &t, double &r, double &A)
-{
-    const bool tl = __double2loint(v.x) & 1, al = __double2loint(v.y) & 1;
-    const double big = (1.0 - v.x) - v.y;
-    t = tl ? big : v.x;
-    A = al ? big : v.y;
-    r = tl ? v.x : (al ? v.y : big);
-}
-
 // Workgroup of request r with first[r] <= g < first[r+1] (batched launches).
 __device__ __forceinline__ int batch_request(const int *first, int n, int g)
 {

@@ -396,8 +396,9 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
                              __hiloint2double(__float_as_int(Ly.A), __float_as_int(Ly.omr)));
             y = make_double2(__hiloint2double(__float_as_int(Ly.Sdn), __float_as_int(Ly.Sup)), 0.0);
         } else {
-            map.step(Ly.t, Ly.r, Ly.t + Ly.A, Ly.A, Ly.Sup, Ly.Sdn);
-            x = pack_tra(Ly.t, Ly.r, Ly.A);
+            map.step(Ly.t, Ly.r, Ly.omr, Ly.A, Ly.Sup, Ly.Sdn);
+            const StoredLayer c = store_layer(Ly.t, Ly.r, Ly.A);
+            x = make_double2(c.p, c.q);
             y = make_double2(Ly.Sup, Ly.Sdn);
         }
         at(p_rec, o_st) = x;
@@ -480,9 +481,9 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
                 auto hi_f = [](double v) { return double(__int_as_float(__double2hiint(v))); };
                 rec = elim_step(st, lo_f(x[k].x), hi_f(x[k].x), lo_f(x[k].y), hi_f(x[k].y), lo_f(y[k].x), hi_f(y[k].x));
             } else {
-                double t, r, A;
-                unpack_tra(x[k], t, r, A);
-                rec = elim_step(st, t, r, t + A, A, y[k].x, y[k].y);
+                double t, r, omr, A;
+                load_layer({x[k].x, x[k].y}, t, r, omr, A);
+                rec = elim_step(st, t, r, omr, A, y[k].x, y[k].y);
             }
             double2 *r = records() + (long long)(N - 1 - a_last - q) * 2 * RB;
             at(r, o_rec) = make_double2(rec.G, rec.H);
