@@ -298,16 +298,53 @@ extern "C" const char *rt_status_string(rt_status s)
 // AUTO on a stream-ordered solve: the deep kernel where the layer kernel's
 // workgroups (about one per column up to one per compute unit) would leave
 // most of the chip idle for a long sweep.
-static bool prefer_deep(const rt_handle *h, int C, int N)
+static bool prefer_deep(const rtk::DeviceLimits &dev, int C, int N)
 {
-    return N >= kDeepMinSlabs && (long long)C * kDeepColsPerCu <= h->dev.n_cu;
+    return N >= kDeepMinSlabs && (long long)C * kDeepColsPerCu <= dev.n_cu;
+}
+
+// Where AUTO may take the deep kernel (prefer_deep), FP64 takes the stream kernel on
+// shorter or more columns, whose segments in one workgroup are done before the deep path's
+// launches (us, deep | stream, columns x slabs x lanes: 16 x 80 x 30: 36 | 32, 16 x 100 x 30:
+// 36 | 40, 128 x 200 x 30: 89 | 60, 16 x 40 x 64: 35 | 31, 16 x 60 x 64: 35 | 44; in
+// rt_deep.hip's seven launches 16 x 80 x 100: 53 | 54, 16 x 100 x 100: 49 | 60, 4 x 100 x
+// 300: 74 | 63, 4 x 130 x 300: 75 | 81, 16 x 200 x 300: 154 | 118).  In mixed precision the
+// paths round differently (the deep one keeps 1 - t of thin layers), so AUTO's results stay
+// the deep path's.
+static bool deep_beats_stream(int C, int N, int NB, int precision, const rtk::Geometry &g, const rtk::DeviceLimits &dev)
+{
+    if (precision != RT_FP64 || g.threads == 0) return true;
+    const long long lanes = (long long)C * NB;
+    if (NB > 64) return N >= 64 + NB / 4 && lanes <= 3200;
+    return 4ll * C <= dev.n_cu && N >= (NB > 32 ? 48 : 88);
+}
+
+// The kernel and launch of a default tile (may_deep: AUTO, else the layer kernel's).
+rtk::Geometry rtk::default_geometry(int C, int N, int NB, int NG, bool may_deep, int precision, const DeviceLimits &dev)
+{
+    Geometry gs = stream_geometry(C, N, NB, NG, precision == RT_MIXED, dev);
+    if (may_deep && prefer_deep(dev, C, N)) {
+        const Geometry deep = deep_geometry(C, N, NB, dev);
+        if (deep.threads == 0 || deep_beats_stream(C, N, NB, precision, gs, dev)) return deep;
+        gs.scratch = std::max(gs.scratch, deep.scratch);   // AUTO's at this size, as rt_work_bytes states it
+        return gs;
+    }
+    const Geometry g = solve_geometry(C, N, NB, 0, KERNEL_LAYER, precision, dev, NG);
+    // the layer kernel where the stream kernel is refused or estimated to be done later: 4 to 8
+    // layers on small grids, a few lanes per column (padded to 8) on large ones, columns
+    // whose level sums leave it few wavefronts (us, layer | stream, FP64: 20 x 5 x 30: 16.2 | 16.7,
+    // 10242 x 40 x 2: 65 | 116; mixed: 20 x 5 x 100: 18.0 | 20.4, 20000 x 120 x 5: 408 | 654,
+    // 10242 x 120 x 10: 376 | 467)
+    if (gs.threads == 0 || g.threads == 0 || (N >= 4 && g.us < gs.us)) return g;
+    gs.scratch = std::max(gs.scratch, g.scratch);   // the same records
+    return gs;
 }
 
 extern "C" int64_t rt_work_bytes(const rt_handle *h, int32_t n_cols, int32_t n_layers)
 {
     if (!h || n_cols < 1 || n_layers < 1 || n_layers > kMaxLayers) return -1;
     const rtk::Geometry g =
-        prefer_deep(h, n_cols, n_layers)
+        prefer_deep(h->dev, n_cols, n_layers)
             ? rtk::deep_geometry(n_cols, n_layers, h->NBG, h->dev)
             : rtk::solve_geometry(n_cols, n_layers, h->NBG, 0, rtk::KERNEL_AUTO, RT_FP64, h->dev,
                                   h->NG);
@@ -458,41 +495,15 @@ extern "C" rt_status rt_destroy(rt_handle *h)
 // Slabs of a request: one per layer, two on the sub-layer grid.
 static int request_slabs(const rt_request *r) { return r->T_center ? 2 * r->n_layers : r->n_layers; }
 
-// Where AUTO may take the deep kernel (prefer_deep), FP64 takes the stream kernel on
-// shorter or more columns, whose segments in one workgroup are done before the deep path's
-// launches (us, deep | stream, columns x slabs x lanes: 16 x 80 x 30: 36 | 32, 16 x 100 x 30:
-// 36 | 40, 128 x 200 x 30: 89 | 60, 16 x 40 x 64: 35 | 31, 16 x 60 x 64: 35 | 44; in
-// rt_deep.hip's seven launches 16 x 80 x 100: 53 | 54, 16 x 100 x 100: 49 | 60, 4 x 100 x
-// 300: 74 | 63, 4 x 130 x 300: 75 | 81, 16 x 200 x 300: 154 | 118).  In mixed precision the
-// paths round differently (the deep one keeps 1 - t of thin layers), so AUTO's results stay
-// the deep path's.
-static bool deep_beats_stream(const rt_handle *h, const rt_request *r, int N)
-{
-    if (r->precision != RT_FP64) return true;
-    const long long lanes = (long long)r->n_cols * h->NBG;
-    if (h->NBG > 64) return N >= 64 + h->NBG / 4 && lanes <= 3200;
-    return 4ll * r->n_cols <= h->dev.n_cu && N >= (h->NBG > 32 ? 48 : 88);
-}
-
 static rtk::Geometry request_geometry(const rt_handle *h, const rt_request *r)
 {
     const int N = request_slabs(r);
-    rtk::Geometry deep{};
-    if (r->kernel == RT_KERNEL_DEEP ||
-        (r->kernel == RT_KERNEL_AUTO && r->cols_per_block == 0 && prefer_deep(h, r->n_cols, N))) {
-        deep = rtk::deep_geometry(r->n_cols, N, h->NBG, h->dev);
-        if (r->kernel == RT_KERNEL_DEEP || deep.threads == 0 || deep_beats_stream(h, r, N)) return deep;
-    }
-    const int kernel = r->kernel == RT_KERNEL_LANE ? rtk::KERNEL_LANE : rtk::KERNEL_LAYER;
-    const rtk::Geometry g = rtk::solve_geometry(r->n_cols, N, h->NBG, r->cols_per_block, kernel,
-                                                r->precision, h->dev, h->NG);
-    if (kernel == rtk::KERNEL_LANE || r->cols_per_block != 0 || (g.threads == 0 && deep.threads == 0)) return g;
-    rtk::Geometry gs = rtk::stream_geometry(r->n_cols, N, h->NBG, h->NG, r->precision == RT_MIXED, h->dev);
-    if (gs.threads == 0) return deep.threads > 0 ? deep : g;
-    // the layer kernel's reservation, which holds the same records, or the work buffer of
-    // AUTO at this size, as rt_work_bytes states it
-    gs.scratch = std::max(gs.scratch, deep.threads > 0 ? deep.scratch : g.scratch);
-    return gs;
+    if (r->kernel == RT_KERNEL_DEEP) return rtk::deep_geometry(r->n_cols, N, h->NBG, h->dev);
+    if (r->kernel == RT_KERNEL_LANE || r->cols_per_block != 0)
+        return rtk::solve_geometry(r->n_cols, N, h->NBG, r->cols_per_block,
+                                   r->kernel == RT_KERNEL_LANE ? rtk::KERNEL_LANE : rtk::KERNEL_LAYER,
+                                   r->precision, h->dev, h->NG);
+    return rtk::default_geometry(r->n_cols, N, h->NBG, h->NG, r->kernel == RT_KERNEL_AUTO, r->precision, h->dev);
 }
 
 static hipError_t launch(const rtk::SolveArgs &a, const rtk::Geometry &g, int precision,
@@ -1141,7 +1152,7 @@ extern "C" rt_status rt_submit(rt_handle *h, const rt_request *r, uint64_t *tick
     // the others (deep and lane kernels, FP32 inputs) run as batched launches
     bool worker = false;
     if (h->cfg.serve_mode == RT_SERVE_PERSISTENT && !h->wbroken &&
-        !(r->kernel == RT_KERNEL_AUTO && r->cols_per_block == 0 && prefer_deep(h, r->n_cols, request_slabs(r))) &&
+        !(r->kernel == RT_KERNEL_AUTO && r->cols_per_block == 0 && prefer_deep(h->dev, r->n_cols, request_slabs(r))) &&
         (j.g.kernel == rtk::KERNEL_LAYER || j.g.kernel == rtk::KERNEL_STREAM) &&
         r->input_dtype == RT_F64) {
         const rtk::Geometry gw = rtk::worker_geometry(r->n_cols, request_slabs(r), h->NBG, r->precision,

@@ -21,8 +21,8 @@ enum Kernel : int {
                         // shared by the workgroup; only the elimination is per lane
     KERNEL_DEEP = 3,    // a column's layers split into segments on separate
                         // workgroups, the recurrences composed per segment
-    KERNEL_STREAM = 4,  // a wavefront owns 64 lanes for the whole sweep (the layer
-                        // kernel's default tile on grids that fill the chip)
+    KERNEL_STREAM = 4,  // a wavefront owns 64 lanes for the whole sweep of a column or
+                        // of a segment of one (most default tiles)
 };
 
 // Everything one solve kernel needs (passed by value).
@@ -107,14 +107,16 @@ struct DeviceLimits {
 
 // Launch geometry of a solve for a problem shape.
 struct Geometry {
-    int kernel;     // KERNEL_LANE, KERNEL_LAYER or KERNEL_DEEP
+    int kernel;     // KERNEL_LANE, KERNEL_LAYER, KERNEL_DEEP or KERNEL_STREAM
     int K;          // columns per workgroup
-    int PC, CH;     // layer kernel: levels per chunk, interfaces per bin-sum pass
+    int PC, CH;     // layer kernel: levels per chunk, interfaces per bin-sum pass;
+                    // stream kernel: segments per column, layers per segment
     int threads;    // workgroup size (multiple of 64)
     int blocks;     // workgroups
     long long lanes;
     size_t lds;     // dynamic LDS bytes
     size_t scratch; // work-buffer bytes for N layers (set by solve_geometry)
+    double us;      // estimated time (layer and stream kernels' default tiles)
 };
 
 constexpr int kMaxThreads = 1024;      // workgroup size bound of the solve kernels
@@ -127,6 +129,8 @@ constexpr int kMaxTileLanes = 1024;    // (column, bin) lanes of one layer-kerne
 Geometry solve_geometry(int C, int N, int NB, int K, int kernel, int precision,
                         const DeviceLimits &dev, int NG = 1);
 hipError_t launch_solve(const SolveArgs &a, const Geometry &g, int precision, hipStream_t s);
+// The default tile's kernel and launch: layer, stream or (may_deep) deep.
+Geometry default_geometry(int C, int N, int NB, int NG, bool may_deep, int precision, const DeviceLimits &dev);
 // Wavefront-per-lanes solve (threads = 0: the shape does not fit it).
 Geometry stream_geometry(int C, int N, int NB, int NG, bool mixed, const DeviceLimits &dev);
 hipError_t launch_stream(const SolveArgs &a, const Geometry &g, int precision, hipStream_t s);

@@ -743,10 +743,43 @@ static Geometry stream_shape(int C, int N, int NB, int NG, int S, bool direct, b
     return g;
 }
 
-// Segments per column: as many as bring the chip's 12 wavefronts per CU (three per
-// SIMD: 168 registers) and no more, since a second round of workgroups costs more
-// than the segments give (us, C x N x NB, FP64 by S; the first is one wavefront per CU
-// or less at S = 1):
+// Estimated time of a launch, us.  A compute unit holds wg workgroups at once (12 wavefronts,
+// three per SIMD at 168 registers; 16 unsegmented in mixed precision; fewer where the level sums
+// fill its LDS), in rounds; c wavefronts per SIMD take layer + layer_c c for each layer of a
+// segment and chunk + chunk_c c for each chunk of levels.  A full round of segments costs
+// more than the last one, whose records the caches hold.  Coefficients: least squares of
+// measured times, 1 to 1000 layers, 1 to 300 lanes, up to 30000 columns (8 percent rms in FP64, 9 in
+// mixed precision, 10 in segments).
+static double stream_time(const Geometry &g, int C, int N, int NB, bool mixed, const DeviceLimits &dev)
+{
+    struct Fit {
+        double base, seg, half, wide, layer, layer_c, chunk, chunk_c, round;   // half: 33 to 64 lanes per column
+    };
+    static constexpr Fit fits[2][2] = {{{6.5, 0.0, 0.8, 4.0, 1.07, 0.45, 0.0, 2.4, 0.9}, {8.7, 0.25, 0.8, 3.5, 1.35, 0.46, 0.0, 3.4, 1.03}},
+                                       {{7.0, 0.2, 3.0, 5.7, 0.98, 0.38, 0.17, 1.78, 1.0}, {9.3, 0.2, 3.0, 5.1, 1.25, 0.35, 0.05, 2.13, 1.17}}};
+    const Fit &f = fits[mixed][g.PC > 1];
+    const int n_cu = dev.n_cu > 0 ? dev.n_cu : 256, w = g.threads / 64;
+    const int tiles = NB > 64 ? C * lane_layout(NB).NBw : (C + g.K - 1) / g.K, per_cu = (tiles + n_cu - 1) / n_cu;
+    const int wg = std::max(1, std::min((mixed && g.PC == 1 ? 16 : 12) / w, (int)(dev.lds / g.lds)));
+    const int full = (per_cu - 1) / wg, odd = g.CH & 1;
+    const int chunks = 1 + std::max(0, g.CH - odd - (kChunk - 2 - 2 * odd) + kChunk - 1) / kChunk;
+    auto round = [&](double c) {
+        c = std::max(1.0, c);
+        return g.CH * (f.layer + f.layer_c * c) + chunks * (f.chunk + f.chunk_c * c);
+    };
+    // (segments of a few lanes read and write pieces of cache lines)
+    const double rounds = full * f.round * (g.PC > 1 && NB <= 16 ? 1.5 : 1.0);
+    const double us = f.base + f.seg * g.PC + (NB > 64 ? f.wide : NB > 32 ? f.half : 0.0) + rounds * round(wg * w / 4.0) +
+                      round(((per_cu - full * wg) * w + 3) / 4);
+    // inputs and records, and the coefficients of all segments but the first, from memory (beyond
+    // the caches' reach; 4.5 TB/s)
+    const double bytes = (double)C * N * NB * (88.0 + 64.0 * (g.PC - 1) / g.PC);
+    return bytes > 1e9 ? std::max(us, bytes / 4.5e6) : us;
+}
+
+// Segments per column: the least estimated time, where the most segments whose wavefronts
+// the registers hold count a tenth less (us, C x N x NB, FP64 by S; the first is one
+// wavefront per CU or less at S = 1):
 //   162 x 40 x 30      1: 92    2: 58    4: 38    8: 27   16: 30
 //   512 x 40 x 30      1: 93    2: 64    4: 42    8: 35   16: 58
 //   1500 x 40 x 30     1: 94    2: 81    3: 75    4: 65    8: 73
@@ -755,9 +788,11 @@ static Geometry stream_shape(int C, int N, int NB, int NG, int S, bool direct, b
 //   3200 x 40 x 30     1: 124   2: 148
 //   100 x 60 x 300     1: 141   2: 117   3: 88    4: 76    5: 109
 //   300 x 100 x 16     1: 221   4: 79    8: 58   16: 45   20: 62
+//   162 x 20 x 100     4: 32    8: 48 (workgroups of eight wavefronts, one per CU: two rounds)
 // (5 and 20 give workgroups of five wavefronts, which pack badly on four SIMDs.)  Short
 // segments give less than their hand-over costs: 48 layers take 27 in 8 segments and 29
-// in 16, 60 layers 35 and 31; 20 layers 24 in 4 and 22 in 8; 12 layers 21.7 in 4, 24 in 2.
+// in 16, 60 layers 35 and 31; 20 layers 24 in 4 and 22 in 8; 12 layers 21.7 in 4, 24 in 2;
+// 5 layers 17.8 in 2 and 16.7 in 1.
 // Up to 4 segments, a workgroup takes as many columns as a wavefront holds groups,
 // so that its first wavefront eliminates as it goes (2562 x 40 x 30: 110 to 102,
 // mixed 91 to 76; 3000 x 60 x 16: 121 to 91); with 8 the larger workgroup costs more
@@ -766,16 +801,27 @@ Geometry stream_geometry(int C, int N, int NB, int NG, bool mixed, const DeviceL
 {
     static constexpr struct {
         int S, layers;
-    } splits[] = {{16, 56}, {8, 20}, {4, 8}, {3, 6}, {2, 4}};
+    } splits[] = {{16, 48}, {8, 20}, {4, 7}, {3, 9}, {2, 8}, {1, 1}};
     const LaneLayout ll = lane_layout(NB);
     const int n_cu = dev.n_cu > 0 ? dev.n_cu : 256;
     const long long waves = NB > 64 ? (long long)C * ll.NBw : (C + ll.gw - 1) / ll.gw;
+    Geometry best{};
+    bool fits = false;   // a split whose wavefronts the registers hold was met
+    double least = 0.0;
     for (const auto &v : splits) {
-        if (N < v.layers || waves * v.S > 12ll * n_cu) continue;
-        const Geometry g = stream_shape(C, N, NB, NG, v.S, v.S <= 4, mixed, dev);
-        if (g.threads > 0) return g;
+        if (N < v.layers) continue;
+        Geometry g = stream_shape(C, N, NB, NG, v.S, v.S > 1 && v.S <= 4, mixed, dev);
+        if (g.threads == 0) continue;
+        g.us = stream_time(g, C, N, NB, mixed, dev);
+        const bool first = !fits && waves * v.S <= 12ll * n_cu;
+        fits = fits || first;
+        const double us = first ? g.us / 1.1 : g.us;
+        if (best.threads == 0 || us < least) {
+            best = g;
+            least = us;
+        }
     }
-    return stream_shape(C, N, NB, NG, 1, false, mixed, dev);
+    return best;
 }
 
 hipError_t launch_stream(const SolveArgs &a, const Geometry &g, int precision, hipStream_t s)

@@ -31,8 +31,10 @@ def compare(w, out, mixed, opts=None):
 # (columns, layers, lanes, compute units) -> segments per column: padding of 8 to 64 lanes, wide
 # columns, ragged last workgroups, odd and uneven segments
 STREAM = [((9, 3, 1, 1), 1), ((55, 11, 7, 1), 1), ((30, 16, 16, 1), 1), ((7, 17, 33, 1), 1), ((4, 9, 65, 1), 1), ((3, 8, 130, 1), 1),
-          ((3, 5, 30, 256), 2), ((17, 4, 8, 256), 2), ((3, 7, 30, 256), 3), ((9, 6, 9, 256), 3), ((5, 9, 30, 256), 4),
-          ((7, 13, 7, 256), 4), ((2, 19, 100, 256), 4), ((3, 23, 30, 256), 8), ((9, 25, 5, 256), 8), ((1, 21, 70, 256), 8),
+          ((37, 8, 5, 1), 2), ((21, 9, 16, 1), 2), ((6, 17, 33, 1), 2), ((4, 8, 65, 2), 2), ((6, 23, 65, 2), 2),
+          ((29, 17, 5, 1), 3), ((15, 13, 9, 1), 3), ((7, 17, 30, 1), 3), ((4, 13, 100, 2), 3),
+          ((1, 7, 5, 1), 4), ((5, 9, 30, 256), 4), ((7, 13, 7, 256), 4), ((2, 19, 100, 256), 4),
+          ((3, 23, 30, 256), 8), ((9, 25, 5, 256), 8), ((1, 21, 70, 256), 8),
           ((3, 57, 7, 256), 16), ((2, 61, 30, 256), 16)]
 
 
