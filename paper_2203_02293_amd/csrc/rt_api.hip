@@ -303,20 +303,24 @@ static bool prefer_deep(const rtk::DeviceLimits &dev, int C, int N)
     return N >= kDeepMinSlabs && (long long)C * kDeepColsPerCu <= dev.n_cu;
 }
 
-// Where AUTO may take the deep kernel (prefer_deep), FP64 takes the stream kernel on
-// shorter or more columns, whose segments in one workgroup are done before the deep path's
-// launches (us, deep | stream, columns x slabs x lanes: 16 x 80 x 30: 36 | 32, 16 x 100 x 30:
-// 36 | 40, 128 x 200 x 30: 89 | 60, 16 x 40 x 64: 35 | 31, 16 x 60 x 64: 35 | 44; in
-// rt_deep.hip's seven launches 16 x 80 x 100: 53 | 54, 16 x 100 x 100: 49 | 60, 4 x 100 x
-// 300: 74 | 63, 4 x 130 x 300: 75 | 81, 16 x 200 x 300: 154 | 118).  In mixed precision the
-// paths round differently (the deep one keeps 1 - t of thin layers), so AUTO's results stay
-// the deep path's.
+// Where AUTO may take the deep kernel (prefer_deep), FP64 takes the stream kernel, in
+// geometry g, where a column's segments in one workgroup are done before the deep path's
+// launches: short columns (us, deep | stream, columns x slabs x lanes: 16 x 80 x 30: 36 | 32,
+// 16 x 100 x 30: 36 | 40, 16 x 40 x 64: 35 | 31, 16 x 60 x 64: 35 | 44; in rt_deep.hip's seven
+// launches 16 x 80 x 100: 53 | 54, 4 x 100 x 300: 74 | 63), and more columns or lanes, which
+// the deep path's time grows with, while a segment is short enough (128 x 200 x 30: 89 | 60,
+// 65 x 2000 x 30: 594 | 413, 65 x 4096 x 30: 1157 | 1263, 96 x 4096 x 40: 1783 | 2407; 16 x 1000 x
+// 300: 507 | 436, 11 x 1000 x 300: 363 | 418, 16 x 4096 x 300: 1959 | 2587, 40 x 4096 x 100:
+// 1723 | 2552).  The times below are fits of such figures.  In mixed precision the paths
+// round differently (the deep one keeps 1 - t of thin layers), so AUTO's results stay the
+// deep path's.
 static bool deep_beats_stream(int C, int N, int NB, int precision, const rtk::Geometry &g, const rtk::DeviceLimits &dev)
 {
     if (precision != RT_FP64 || g.threads == 0) return true;
-    const long long lanes = (long long)C * NB;
-    if (NB > 64) return N >= 64 + NB / 4 && lanes <= 3200;
-    return 4ll * C <= dev.n_cu && N >= (NB > 32 ? 48 : 88);
+    const double items = (double)C * N * NB, L = g.CH;
+    const double stream_us = std::min(8.0 + 4.0 * L, 21.0 + (g.threads > 256 ? 3.4 : 2.5) * L);
+    if (NB > 64) return N >= 64 + NB / 4 && 28.0 + 0.15 * NB + 1e-4 * std::max(0.0, items - 2e5) < 0.95 * stream_us;
+    return N >= (NB > 32 ? 48 : 88) && (4ll * C <= dev.n_cu || (NB > 16 && 30.0 + 1.15e-4 * items < stream_us));
 }
 
 // The kernel and launch of a default tile (may_deep: AUTO, else the layer kernel's).

@@ -56,7 +56,10 @@ LINES = [((42, 12, 7, 0), STREAM, 4), ((162, 40, 30, 0), STREAM, 8), ((2562, 40,
          ((162, 20, 100, 0), STREAM, 4), ((100, 20, 100, 0), STREAM, 8),
          # deep columns
          ((1, 4096, 30, 0), DEEP, 0), ((16, 1000, 30, 1), DEEP, 0), ((16, 40, 30, 1), DEEP, 0), ((64, 87, 30, 0), STREAM, 16),
-         ((64, 88, 30, 0), DEEP, 0), ((3, 47, 40, 0), STREAM, 8), ((3, 48, 40, 0), DEEP, 0)]
+         ((64, 88, 30, 0), DEEP, 0), ((3, 47, 40, 0), STREAM, 8), ((3, 48, 40, 0), DEEP, 0),
+         # FP64 above a quarter of the compute units, or 3200 lanes: by the layers
+         ((96, 2000, 30, 0), STREAM, 16), ((65, 4096, 30, 0), DEEP, 0), ((16, 1000, 300, 0), STREAM, 8), ((16, 4096, 300, 0), DEEP, 0),
+         ((11, 400, 300, 0), STREAM, 8), ((11, 1000, 300, 0), DEEP, 0), ((40, 4096, 100, 0), DEEP, 0), ((128, 1000, 100, 0), STREAM, 8)]
 
 
 @pytest.mark.parametrize("shape,kernel,S", LINES, ids=["x".join(map(str, c[0])) for c in LINES])
