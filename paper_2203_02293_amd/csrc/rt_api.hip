@@ -319,7 +319,7 @@ static bool deep_beats_stream(int C, int N, int NB, int precision, const rtk::Ge
     if (precision != RT_FP64 || g.threads == 0) return true;
     const double items = (double)C * N * NB, L = g.CH;
     const double stream_us = std::min(8.0 + 4.0 * L, 21.0 + (g.threads > 256 ? 3.4 : 2.5) * L);
-    if (NB > 64) return N >= 64 + NB / 4 && 28.0 + 0.15 * NB + 1e-4 * std::max(0.0, items - 2e5) < 0.95 * stream_us;
+    if (NB > 64) return N >= (C < 4 ? 64 : 40) + NB / 4 && 28.0 + 0.15 * NB + 1e-4 * std::max(0.0, items - 2e5) < 0.95 * stream_us;
     return N >= (NB > 32 ? 48 : 88) && (4ll * C <= dev.n_cu || (NB > 16 && 30.0 + 1.15e-4 * items < stream_us));
 }
 
@@ -334,12 +334,13 @@ rtk::Geometry rtk::default_geometry(int C, int N, int NB, int NG, bool may_deep,
         return gs;
     }
     const Geometry g = solve_geometry(C, N, NB, 0, KERNEL_LAYER, precision, dev, NG);
-    // the layer kernel where the stream kernel is refused or estimated to be done later: 4 to 8
+    // the layer kernel where the stream kernel is refused or estimated to be done later (the two
+    // estimates scatter alike; at 0.97 as many measured shapes lose by either choice): 4 to 8
     // layers on small grids, a few lanes per column (padded to 8) on large ones, columns
     // whose level sums leave it few wavefronts (us, layer | stream, FP64: 20 x 5 x 30: 16.2 | 16.7,
     // 10242 x 40 x 2: 65 | 116; mixed: 20 x 5 x 100: 18.0 | 20.4, 20000 x 120 x 5: 408 | 654,
     // 10242 x 120 x 10: 376 | 467)
-    if (gs.threads == 0 || g.threads == 0 || (N >= 4 && g.us < gs.us)) return g;
+    if (gs.threads == 0 || g.threads == 0 || (N >= 4 && g.us < 0.97 * gs.us)) return g;
     gs.scratch = std::max(gs.scratch, g.scratch);   // the same records
     return gs;
 }

@@ -768,13 +768,13 @@ static double stream_time(const Geometry &g, int C, int N, int NB, bool mixed, c
         return g.CH * (f.layer + f.layer_c * c) + chunks * (f.chunk + f.chunk_c * c);
     };
     // (segments of a few lanes read and write pieces of cache lines)
-    const double rounds = full * f.round * (g.PC > 1 && NB <= 16 ? 1.5 : 1.0);
+    const double rounds = full * f.round * (g.PC > 1 && NB <= 16 ? 2.0 : 1.0);
     const double us = f.base + f.seg * g.PC + (NB > 64 ? f.wide : NB > 32 ? f.half : 0.0) + rounds * round(wg * w / 4.0) +
                       round(((per_cu - full * wg) * w + 3) / 4);
-    // inputs and records, and the coefficients of all segments but the first, from memory (beyond
-    // the caches' reach; 4.5 TB/s)
+    // inputs and records, and the coefficients of all segments but the first, from memory (where
+    // they are many times the caches; 3.8 TB/s)
     const double bytes = (double)C * N * NB * (88.0 + 64.0 * (g.PC - 1) / g.PC);
-    return bytes > 1e9 ? std::max(us, bytes / 4.5e6) : us;
+    return bytes > 3e9 ? std::max(us, bytes / 3.8e6) : us;
 }
 
 // Segments per column: the least estimated time, where the most segments whose wavefronts
