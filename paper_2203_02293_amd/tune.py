@@ -2,8 +2,11 @@
 
 For each representative shape (columns, layers, bins) and precision it times
 rt_solve_fluxes with each kernel and every admissible tile width K and
-records the fastest in ``tuning.json`` next to this file.  The binding
-(``rt.tuned_launch``) picks the entry nearest to a request's shape.
+records the fastest in ``tuning.json`` next to this file: AUTO's own choice unless another
+one is at least MARGIN faster.  The binding (``rt.tuned_launch``) picks the entry nearest to a
+request's shape, so AUTO's choice is recorded as the layer kernel's default tile where that is
+what it ran, and as AUTO (kernel 0) where it ran the deep kernel: its rules draw that line
+for the shapes around.
 
     python -m paper_2203_02293_amd.tune [--quick]
 """
@@ -27,10 +30,14 @@ SHAPES = [  # (columns, layers, bins): GCM size, serving mix corners, high resol
 ]
 
 
+MARGIN = 0.03   # two sweeps of one build differ by up to 2 percent
+AUTO = (rt.RT_KERNEL_AUTO, 0)
+
+
 def candidates(nb: int, n_cols: int) -> list[tuple[int, int]]:
-    """(kernel, K) pairs: the layer kernel's default tile and a spread around it,
+    """(kernel, K) pairs: AUTO, the layer kernel's default tile and a spread around it,
     the lane kernel's tiles (K * bins <= 512) and the deep kernel."""
-    out = [(rt.RT_KERNEL_LAYER, 0), (rt.RT_KERNEL_DEEP, 0)]
+    out = [AUTO, (rt.RT_KERNEL_LAYER, 0), (rt.RT_KERNEL_DEEP, 0)]
     out += [(rt.RT_KERNEL_LAYER, k) for k in (1, 2, 3, 4, 6, 8, 10, 11, 12, 16, 24, 32)
             if k * nb <= 1024 and k <= n_cols]
     out += [(rt.RT_KERNEL_LANE, k) for k in (1, 2, 4, 8, 16)
@@ -73,15 +80,19 @@ def main(argv=None):
         out = s.outputs(C, N)
         for prec in (rt.RT_FP64, rt.RT_MIXED):
             times = {}
-            for cand in candidates(NB, C):
-                t = time_one(s, inp, out, prec, cand, args.reps, torch)
-                if t is not None:
-                    times[cand] = t
+            for _ in range(3):   # the first candidate would find an idle device's clock
+                for cand in candidates(NB, C):
+                    t = time_one(s, inp, out, prec, cand, args.reps, torch)
+                    if t is not None:
+                        times[cand] = min(t, times.get(cand, t))
             best = min(times, key=times.get)
+            if times[best] > (1.0 - MARGIN) * times[AUTO]:
+                deep = s.kernel_for(inp, out, prec, 0, rt.RT_KERNEL_AUTO) == rt.RT_KERNEL_DEEP
+                best = AUTO if deep else (rt.RT_KERNEL_LAYER, 0)
             entries.append(dict(n_cols=C, n_layers=N, n_bins=NB, precision=prec,
                                 kernel=best[0], cols_per_block=best[1], ms=times[best]))
-            name = {rt.RT_KERNEL_LANE: "lane", rt.RT_KERNEL_LAYER: "layer",
-                    rt.RT_KERNEL_DEEP: "deep"}
+            name = {rt.RT_KERNEL_AUTO: "auto", rt.RT_KERNEL_LANE: "lane",
+                    rt.RT_KERNEL_LAYER: "layer", rt.RT_KERNEL_DEEP: "deep"}
             report.append(dict(shape=[C, N, NB], precision=prec,
                                ms={f"{name[kk]}:{k}": round(v, 4) for (kk, k), v in times.items()},
                                best=[name[best[0]], best[1]]))

@@ -82,3 +82,14 @@ def test_reservation_is_the_former_kernels():
                         former = deep(C, N, NB)
                     assert (g.threads > 0) == (former.threads > 0)
                     assert g.scratch == former.scratch and g.lds <= LDS, (C, N, NB, NG, mixed)
+
+
+def test_tuned_entries_follow_the_line():
+    """The autotuner's table, applied to shapes around its entries, sends no FP64 request to the other
+    side of AUTO's line between the deep and the stream kernel."""
+    for NB in (30, 100, 300):
+        for C in (1, 8, 20, 40, 64, 65, 100, 128, 129):
+            for N in (40, 60, 100, 150, 250, 300, 400, 1000, 4096):
+                kernel, K = rt.tuned_launch(NB, rt.RT_FP64, C, N)
+                if kernel != rt.RT_KERNEL_AUTO:
+                    assert K == 0 and (kernel == rt.RT_KERNEL_DEEP) == (default(C, N, NB).kernel == DEEP), (C, N, NB, kernel)
