@@ -728,7 +728,7 @@ extern "C" rt_status rt_optical_properties(rt_handle *h, const rt_optics_request
     a.dtau = r->dtau;
     a.w0 = r->w0;
     a.g0 = r->g0;
-    const hipError_t e = rtk::launch_optics(a, (hipStream_t)stream);
+    const hipError_t e = rtk::launch_optics(a, h->dev, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(h, e, "optics launch");
     return RT_OK;
 }

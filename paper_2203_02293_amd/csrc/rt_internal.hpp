@@ -99,6 +99,21 @@ __host__ __device__ __forceinline__ void opaque_args(ArgsK &p)
 }
 
 
+// Workgroup of request r with first[r] <= g < first[r+1] (batched launches).
+__host__ __device__ __forceinline__ int batch_request(const int *first, int n, int g)
+{
+    int lo = 0, hi = n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (first[mid] <= g) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// Workgroups go to the device's XCDs, each with an L2 of its own, in turn.
+constexpr int kXcds = 8;
+
 // What the launch shape depends on besides the problem: the device.
 struct DeviceLimits {
     int n_cu;          // compute units
@@ -216,7 +231,7 @@ struct OpticsArgs {
     const double *p, *T, *pc, *Tc;                // [N+1][C], [N][C]
     double *dtau, *w0, *g0;                       // [S][C][NBG]
 };
-hipError_t launch_optics(const OpticsArgs &a, hipStream_t s);
+hipError_t launch_optics(const OpticsArgs &a, const DeviceLimits &dev, hipStream_t s);
 // Gas Rayleigh cross section (x_h2 H2 + x_he He, m^2 per molecule) averaged
 // over [lam_lo, lam_hi] in wavenumber.
 double rayleigh_bin_average(double lam_lo, double lam_hi, double x_h2, double x_he);

@@ -1153,17 +1153,7 @@ __device__ __forceinline__ void solve_tile_layer(const SolveArgs &a, const int t
 }
 
 
-// Workgroup of request r with first[r] <= g < first[r+1] (batched launches).
-__device__ __forceinline__ int batch_slot(const int *first, int n, int g)
-{
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (first[mid] <= g) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
+// Workgroup of request r with first[r] <= g < first[r+1] (batched launches): batch_request.
 
 // MIXED: FP32 coefficients; IN32: FP32 storage of dtau, w0, g0 (mixed only)
 template <bool MIXED, bool IN32 = false>
@@ -1176,7 +1166,7 @@ template <bool MIXED, bool IN32 = false>
 __global__ void __launch_bounds__(kMaxLaneThreads)
 k_solve_lane_batch(const SolveArgs *__restrict__ reqs, const int *__restrict__ first, int n)
 {
-    const int r = batch_slot(first, n, blockIdx.x);
+    const int r = batch_request(first, n, blockIdx.x);
     solve_tile_lane<MIXED, IN32>(reqs[r], blockIdx.x - first[r]);
 }
 
@@ -1190,7 +1180,7 @@ template <bool MIXED, bool IN32 = false>
 __global__ void __launch_bounds__(layer_max_threads(MIXED))
 k_solve_layer_batch(const SolveArgs *__restrict__ reqs, const int *__restrict__ first, int n)
 {
-    const int r = batch_slot(first, n, blockIdx.x);
+    const int r = batch_request(first, n, blockIdx.x);
     solve_tile_layer<MIXED, IN32, true>(reqs[r], blockIdx.x - first[r], reqs[r].status, (ArgsK)(reqs + r));
 }
 

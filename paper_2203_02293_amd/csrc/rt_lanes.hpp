@@ -203,18 +203,6 @@ struct StateMap {
     }
 };
 
-// Workgroup of request r with first[r] <= g < first[r+1] (batched launches).
-__device__ __forceinline__ int batch_request(const int *first, int n, int g)
-{
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (first[mid] <= g) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
 // Outputs of the K columns from c0 on from their level sums, sum(level, 0: up, 1:
 // down or 2: beam, column): the bin-summed fluxes, the net flux, the heating and the
 // flags.  All threads of the workgroup; the sums and s_flag [K] are complete.

@@ -58,7 +58,6 @@ __device__ __forceinline__ Cell cell_at(const OpticsArgs &a, double T, double p)
 }
 
 constexpr int kOpticsThreads = 768;   // workgroup size bound: the most lanes of a column
-constexpr int kXcds = 8;
 constexpr int kOpticsColumns = 1 << 20;   // of one z of the grid (its threads along x: below 2^32)
 constexpr int kOpticsLevels = 64;   // of a workgroup: a lane of its first wavefront each
 
@@ -231,7 +230,7 @@ double rayleigh_bin_average(double lam_lo, double lam_hi, double x_h2, double x_
     return sum / (nu1 - nu0);
 }
 
-hipError_t launch_optics(const OpticsArgs &a, hipStream_t s)
+hipError_t launch_optics(const OpticsArgs &a, const DeviceLimits &dev, hipStream_t s)
 {
     if ((long long)a.S * a.C == 0 || a.NBG == 0) return hipSuccess;
     // Slabs per workgroup, in even runs of at most 16: longer ones spread the stores in
@@ -242,7 +241,7 @@ hipError_t launch_optics(const OpticsArgs &a, hipStream_t s)
     // CU, and three workgroups per two CUs (162 columns, 30 outputs: 4: 10.4, 8: 9.4, 16:
     // 10.2, 40: 14.3).
     const int waves = (a.NBG + 63) / 64;
-    const long long n_cu = 256, want = std::max(n_cu * 6 / waves, n_cu * 3 / 2);
+    const long long n_cu = dev.n_cu > 0 ? dev.n_cu : 256, want = std::max(n_cu * 6 / waves, n_cu * 3 / 2);
     const long long least = std::min<long long>((a.S + 3) / 4, (want + a.C - 1) / a.C);
     const int runs = (int)std::max<long long>((a.S + 15) / 16, least), L = (a.S + runs - 1) / runs;
     const int columns = std::min(a.C, kOpticsColumns);

@@ -654,10 +654,8 @@ constexpr int kColumnThreads = 128;   // of k_stream_columns
 constexpr int kColumnStaticLds = 1024;   // more than its static LDS
 size_t columns_lds(int N) { return 3 * (size_t)(N + 1) * sizeof(double); }
 
-// Workgroups go to the eight XCDs in turn; workgroup g of a grid of 8 n takes tile
-// (g % 8) n + g / 8, so each XCD's L2 sees a run of neighbouring columns (slices of a
-// column share cache lines).
-constexpr int kXcds = 8;
+// Workgroup g of a grid of 8 n takes tile (g % 8) n + g / 8, so each XCD's L2 sees a run of
+// neighbouring columns (slices of a column share cache lines).
 __device__ __forceinline__ int xcd_tile(int g, int n) { return (g % kXcds) * n + g / kXcds; }
 int xcd_grid(int tiles) { return (tiles + kXcds - 1) / kXcds * kXcds; }
 
