@@ -61,18 +61,18 @@ constexpr int kOpticsThreads = 768;   // workgroup size bound: the most lanes of
 constexpr int kOpticsColumns = 1 << 20;   // of one z of the grid (its threads along x: below 2^32)
 constexpr int kOpticsLevels = 64;   // of a workgroup: a lane of its first wavefront each
 
-// L slabs of a column per workgroup, 64 outputs of each per wavefront
-template <bool SUB>
+// L slabs of a column per workgroup, an output of each per thread; ONE: a single wavefront
+// takes them all, 64 at a time
+template <bool SUB, bool ONE>
 __global__ void __launch_bounds__(kOpticsThreads) k_optics(const OpticsArgs a, const int L)
 {
-    // workgroups go to the eight XCDs in turn: each XCD takes a run of the columns of
-    // this blockIdx.z
-    const int per = gridDim.x / kXcds;
-    const int c = blockIdx.z * kOpticsColumns + (blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
+    // each XCD takes a run of the columns of this blockIdx.z; of a few columns, another one
+    // for the next slabs, so that all XCDs have work (1 column, 400 slabs, 600 outputs: 19.2
+    // to 11.2 us; of many columns the sub-layer grid would lose 6 percent)
+    const int per = gridDim.x / kXcds, turn = a.C < 8 * kXcds ? blockIdx.y : 0;
+    const int c = blockIdx.z * kOpticsColumns + (blockIdx.x + turn) % kXcds * per + blockIdx.x / kXcds;
     if (c >= a.C) return;
     const int s0 = blockIdx.y * L, n = min(L, a.S - s0);
-    // this thread's output; the padding takes the last one and stores the same values
-    const int bg = min((int)threadIdx.x, a.NBG - 1);
     const long long row = (long long)a.nT * a.NBG;
     // levels of the slabs, one lane each: centres, or on the sub-layer grid the lower
     // level and then the upper ones (even levels interfaces, odd ones centres)
@@ -98,67 +98,74 @@ __global__ void __launch_bounds__(kOpticsThreads) k_optics(const OpticsArgs a, c
         levels[ln] = {(1 - q.t) * (1 - q.u), q.t * (1 - q.u), (1 - q.t) * q.u, q.t * q.u,
                       q.j * row + (long long)q.i * a.NBG, dp / a.gravity / a.m_mean};
     }
-    const int b = bg / a.NG;
-    const double ss = a.sig_cl_scat[b], sa = a.sig_cl_abs[b], scat = a.sig_gas[b] + ss;
-    const double g0 = scat > 0.0 ? ss * a.g0_cl[b] / scat : 0.0;
-    struct Corners {
-        double k00, k10, k01, k11;
-    };
-    auto load = [&](int k) -> Corners {
-        const int kc = SUB ? min(k, n) : min(k, n - 1);
-        const long long e = levels[kc].at;
-        const double *k0 = a.kappa + ((long long)__builtin_amdgcn_readfirstlane((int)(e >> 32)) << 32 |
-                                      (unsigned)__builtin_amdgcn_readfirstlane((int)e));
-        return {k0[bg], (k0 + a.NBG)[bg], (k0 + row)[bg], (k0 + row + a.NBG)[bg]};
-    };
-    // extinction per gas molecule and albedo at level k: bilinear opacity, then the
-    // mixing of gas and condensate extinction and scattering
-    double ext_lo = 0.0, w0_lo = 0.0;
-    auto level = [&](int k, const Corners &v, double &ext, double &w0) {
-        const Level &m = levels[k];
-        const double kap = m.w00 * v.k00 + m.w10 * v.k10 + m.w01 * v.k01 + m.w11 * v.k11;
-        ext = scat + kap * a.m_mean + sa;
-        w0 = ext > 0.0 ? scat / ext : 0.0;
-    };
-    auto store = [&](int k, double dtau, double w0) {
-        const long long e = ((long long)(s0 + k) * a.C + c) * a.NBG;
-        (a.dtau + e)[bg] = dtau;
-        (a.w0 + e)[bg] = w0;
-        (a.g0 + e)[bg] = g0;
-    };
-    // slab k from level k + SUB's opacities; the next but one level's loads go out
-    // before this slab's stores, into the same registers
-    auto slab = [&](int k, Corners &v) {
-        double ext, w0;
-        level(k + SUB, v, ext, w0);
-        v = load(k + SUB + 2);
+    if constexpr (ONE) __syncthreads();
+    // this thread's output; the padding takes the last one and stores the same values
+    auto output = [&](const int bg) {
+        const int b = bg / a.NG;
+        const double ss = a.sig_cl_scat[b], sa = a.sig_cl_abs[b], scat = a.sig_gas[b] + ss;
+        const double g0 = scat > 0.0 ? ss * a.g0_cl[b] / scat : 0.0;
+        struct Corners {
+            double k00, k10, k01, k11;
+        };
+        auto load = [&](int k) -> Corners {
+            const int kc = SUB ? min(k, n) : min(k, n - 1);
+            const long long e = levels[kc].at;
+            const double *k0 = a.kappa + ((long long)__builtin_amdgcn_readfirstlane((int)(e >> 32)) << 32 |
+                                          (unsigned)__builtin_amdgcn_readfirstlane((int)e));
+            return {k0[bg], (k0 + a.NBG)[bg], (k0 + row)[bg], (k0 + row + a.NBG)[bg]};
+        };
+        // extinction per gas molecule and albedo at level k: bilinear opacity, then the
+        // mixing of gas and condensate extinction and scattering
+        double ext_lo = 0.0, w0_lo = 0.0;
+        auto level = [&](int k, const Corners &v, double &ext, double &w0) {
+            const Level &m = levels[k];
+            const double kap = m.w00 * v.k00 + m.w10 * v.k10 + m.w01 * v.k01 + m.w11 * v.k11;
+            ext = scat + kap * a.m_mean + sa;
+            w0 = ext > 0.0 ? scat / ext : 0.0;
+        };
+        auto store = [&](int k, double dtau, double w0) {
+            const long long e = ((long long)(s0 + k) * a.C + c) * a.NBG;
+            (a.dtau + e)[bg] = dtau;
+            (a.w0 + e)[bg] = w0;
+            (a.g0 + e)[bg] = g0;
+        };
+        // slab k from level k + SUB's opacities; the next but one level's loads go out
+        // before this slab's stores, into the same registers
+        auto slab = [&](int k, Corners &v) {
+            double ext, w0;
+            level(k + SUB, v, ext, w0);
+            v = load(k + SUB + 2);
+            if constexpr (SUB) {
+                store(k, (ext_lo + ext) * levels[k].scale, 0.5 * (w0_lo + w0));
+                ext_lo = ext;
+                w0_lo = w0;
+            } else {
+                store(k, ext * levels[k].scale, w0);
+            }
+        };
+        if constexpr (!ONE) __syncthreads();
+        Corners x = load(0), y = load(1);
         if constexpr (SUB) {
-            store(k, (ext_lo + ext) * levels[k].scale, 0.5 * (w0_lo + w0));
-            ext_lo = ext;
-            w0_lo = w0;
+            level(0, x, ext_lo, w0_lo);
+            x = load(2);
+            int k = 0;
+            for (; k + 2 <= n; k += 2) {
+                slab(k, y);
+                slab(k + 1, x);
+            }
+            if (k < n) slab(k, y);
         } else {
-            store(k, ext * levels[k].scale, w0);
+            int k = 0;
+            for (; k + 2 <= n; k += 2) {
+                slab(k, x);
+                slab(k + 1, y);
+            }
+            if (k < n) slab(k, x);
         }
     };
-    __syncthreads();
-    Corners x = load(0), y = load(1);
-    if constexpr (SUB) {
-        level(0, x, ext_lo, w0_lo);
-        x = load(2);
-        int k = 0;
-        for (; k + 2 <= n; k += 2) {
-            slab(k, y);
-            slab(k + 1, x);
-        }
-        if (k < n) slab(k, y);
-    } else {
-        int k = 0;
-        for (; k + 2 <= n; k += 2) {
-            slab(k, x);
-            slab(k + 1, y);
-        }
-        if (k < n) slab(k, x);
-    }
+    if constexpr (ONE)
+        for (int bg = threadIdx.x; bg < (a.NBG + 63) / 64 * 64; bg += 64) output(min(bg, a.NBG - 1));
+    else output(min((int)threadIdx.x, a.NBG - 1));
 }
 
 // Gauss-Legendre nodes and weights on [-1, 1] by Newton iteration on the
@@ -240,14 +247,19 @@ hipError_t launch_optics(const OpticsArgs &a, const DeviceLimits &dev, hipStream
     // 16: 57, 40: 54).  Fewer, from 4 on, where that leaves the chip idle: six wavefronts per
     // CU, and three workgroups per two CUs (162 columns, 30 outputs: 4: 10.4, 8: 9.4, 16:
     // 10.2, 40: 14.3).
-    const int waves = (a.NBG + 63) / 64;
+    // One or two slabs of many columns do not pay for a workgroup of ten wavefronts that
+    // waits for its brackets (10242 columns x 512 outputs, 1 slab: 54 us, 42 in single ones).
+    const bool one = a.S <= 2 && a.C >= (a.sub ? 4096 : 1024);
+    const int waves = one ? 1 : (a.NBG + 63) / 64;
     const long long n_cu = dev.n_cu > 0 ? dev.n_cu : 256, want = std::max(n_cu * 6 / waves, n_cu * 3 / 2);
     const long long least = std::min<long long>((a.S + 3) / 4, (want + a.C - 1) / a.C);
     const int runs = (int)std::max<long long>((a.S + 15) / 16, least), L = (a.S + runs - 1) / runs;
     const int columns = std::min(a.C, kOpticsColumns);
     const dim3 grid((columns + kXcds - 1) / kXcds * kXcds, (a.S + L - 1) / L, (a.C + kOpticsColumns - 1) / kOpticsColumns);
-    if (a.sub) hipLaunchKernelGGL(k_optics<true>, grid, dim3(64 * waves), 0, s, a, L);
-    else hipLaunchKernelGGL(k_optics<false>, grid, dim3(64 * waves), 0, s, a, L);
+    if (a.sub && one) hipLaunchKernelGGL((k_optics<true, true>), grid, dim3(64), 0, s, a, L);
+    else if (a.sub) hipLaunchKernelGGL((k_optics<true, false>), grid, dim3(64 * waves), 0, s, a, L);
+    else if (one) hipLaunchKernelGGL((k_optics<false, true>), grid, dim3(64), 0, s, a, L);
+    else hipLaunchKernelGGL((k_optics<false, false>), grid, dim3(64 * waves), 0, s, a, L);
     return hipGetLastError();
 }
 

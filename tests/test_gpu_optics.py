@@ -104,6 +104,23 @@ def test_optics_then_solve(rt, torch):
     s.close()
 
 
+# one or two slabs of enough columns for single wavefronts (both grids, a ragged last pass), the
+# first column counts above and below that line, and a few columns whose slabs turn over the XCDs
+@pytest.mark.parametrize("C,N,NB,sublayer", [(1024, 1, 70, False), (1023, 2, 70, False), (1030, 2, 130, False),
+                                             (4096, 1, 70, True), (1, 70, 9, True), (9, 33, 70, False), (63, 19, 5, True), (64, 19, 5, True)])
+def test_optics_few_slabs_few_columns(rt, torch, C, N, NB, sublayer):
+    atm, tab, gw, s = setup(rt, C=C, N=N, NB=NB, NG=1, seed=350 + N)
+    print(f"\n[optics] {C}x{N}x{NB} sublayer={sublayer}", flush=True)
+    out = s.optical_properties(device_atm(torch, atm), sublayer=sublayer)
+    torch.cuda.synchronize()
+    ref = O.optics(atm, tab, sublayer=sublayer)
+    g = {k: v.cpu().numpy() for k, v in out.items()}
+    assert np.max(np.abs(g["dtau"] - ref["dtau"]) / np.maximum(ref["dtau"], 1e-300)) <= OPTICS_REL
+    for k in ("w0", "g0"):
+        assert np.max(np.abs(g[k] - ref[k])) <= OPTICS_ABS
+    s.close()
+
+
 def test_optics_errors(rt, torch):
     spec = synth.Spec(name="o", g_level=1, n_layers=3, n_bins=2, seed=5)
     atm = synth.make_atmosphere(spec, n_cols=2)
