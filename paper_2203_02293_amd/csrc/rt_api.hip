@@ -524,7 +524,8 @@ static hipError_t launch(const rtk::SolveArgs &a, const rtk::Geometry &g, int pr
     }
 }
 
-static rt_status validate(rt_handle *h, const rt_request *r)
+// Checks a request; on RT_OK *geometry is its launch.
+static rt_status validate(rt_handle *h, const rt_request *r, rtk::Geometry *geometry)
 {
     if (!r) return fail(h, RT_EINVAL, "request is NULL");
     if (r->n_cols < 1) return fail(h, RT_EINVAL, "n_cols must be >= 1 (got %d)", r->n_cols);
@@ -543,7 +544,8 @@ static rt_status validate(rt_handle *h, const rt_request *r)
     if (h->NG > 1 && r->kernel == RT_KERNEL_LANE)
         return fail(h, RT_EINVAL, "Gaussian points per bin need the layer kernel");
     if (r->cols_per_block < 0) return fail(h, RT_EINVAL, "cols_per_block must be >= 0");
-    if (request_geometry(h, r).threads == 0)
+    *geometry = request_geometry(h, r);
+    if (geometry->threads == 0)
         return fail(h, RT_EINVAL, "tile of %d columns x %d bins does not fit the %s kernel",
                     r->cols_per_block, h->NBG, r->kernel == RT_KERNEL_LANE ? "lane" : "layer");
     const void *req_in[] = {r->p_iface, r->T_iface, r->dtau, r->w0, r->g0, r->mu_star, r->T_int};
@@ -736,10 +738,10 @@ extern "C" rt_status rt_optical_properties(rt_handle *h, const rt_optics_request
 extern "C" rt_status rt_solve_fluxes(rt_handle *h, const rt_request *r, void *stream)
 {
     if (!h) return RT_EINVAL;
-    rt_status st = validate(h, r);
+    rtk::Geometry g;
+    rt_status st = validate(h, r, &g);
     if (st != RT_OK) return st;
     (void)hipSetDevice(h->cfg.device);
-    const rtk::Geometry g = request_geometry(h, r);
     const size_t need = g.scratch;
     if (need > h->scratch_bytes) {
         // growth waits for the device: earlier solves may still use the old buffer
@@ -760,10 +762,10 @@ extern "C" rt_status rt_solve_fluxes(rt_handle *h, const rt_request *r, void *st
 extern "C" rt_status rt_solve_fluxes_noalloc(rt_handle *h, const rt_request *r, void *stream)
 {
     if (!h) return RT_EINVAL;
-    rt_status st = validate(h, r);
+    rtk::Geometry g;
+    rt_status st = validate(h, r, &g);
     if (st != RT_OK) return st;
     (void)hipSetDevice(h->cfg.device);
-    const rtk::Geometry g = request_geometry(h, r);
     if (g.scratch > kStaticScratchBytes)
         return fail(h, RT_ENOMEM, "request needs a work buffer of %zu bytes; the static one holds %zu",
                     g.scratch, kStaticScratchBytes);
@@ -778,9 +780,10 @@ extern "C" rt_status rt_solve_fluxes_noalloc(rt_handle *h, const rt_request *r, 
 extern "C" int32_t rt_request_kernel(rt_handle *h, const rt_request *r)
 {
     if (!h) return RT_EINVAL;
-    const rt_status st = validate(h, r);
+    rtk::Geometry g;
+    const rt_status st = validate(h, r, &g);
     if (st != RT_OK) return st;
-    switch (request_geometry(h, r).kernel) {
+    switch (g.kernel) {
     case rtk::KERNEL_LANE: return RT_KERNEL_LANE;
     case rtk::KERNEL_DEEP: return RT_KERNEL_DEEP;
     default: return RT_KERNEL_LAYER;
@@ -1137,7 +1140,8 @@ static void pump(rt_handle *h)
 extern "C" rt_status rt_submit(rt_handle *h, const rt_request *r, uint64_t *ticket)
 {
     if (!h || !ticket) return RT_EINVAL;
-    rt_status st = validate(h, r);
+    Job j;
+    rt_status st = validate(h, r, &j.g);
     if (st != RT_OK) return st;
     (void)hipSetDevice(h->cfg.device);
     if ((st = ensure_serving(h)) != RT_OK) return st;
@@ -1149,10 +1153,8 @@ extern "C" rt_status rt_submit(rt_handle *h, const rt_request *r, uint64_t *tick
         if (inflight() >= h->cfg.max_inflight)
             return fail(h, RT_EBUSY, "%d requests in flight", h->cfg.max_inflight);
     }
-    Job j;
     j.ticket = h->next_ticket++;
     j.req = *r;
-    j.g = request_geometry(h, r);
     // the persistent worker takes layer-kernel requests with FP64 input storage;
     // the others (deep and lane kernels, FP32 inputs) run as batched launches
     bool worker = false;

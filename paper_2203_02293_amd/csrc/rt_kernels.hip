@@ -1273,8 +1273,8 @@ double layer_time(const Geometry &g, int N, int NB, bool mixed, const DeviceLimi
 {
     const int n_cu = dev.n_cu > 0 ? dev.n_cu : 256, w = g.threads / 64, T = g.K * NB;
     const int most = std::max(1, std::min((mixed ? 16 : 12) / w, (int)(dev.lds / std::max<size_t>(g.lds, 1))));
-    const int per_cu = (g.blocks + n_cu - 1) / n_cu, rounds = (g.blocks + n_cu * most - 1) / (n_cu * most);
-    const int at_once = std::max(1, per_cu / rounds), chunks = (N + g.PC - 1) / g.PC;
+    const long long per_cu = ((long long)g.blocks + n_cu - 1) / n_cu, rounds = (per_cu + most - 1) / most;
+    const long long at_once = std::max(1ll, per_cu / rounds), chunks = (N + g.PC - 1) / g.PC;
     const double lanes = mixed ? 0.139 : 0.163, layer = mixed ? 0.294 : 0.359;
     return 3.2 + 0.23 * w + rounds * (5.3 + 4.2 * chunks + N * (lanes * T / 64 * at_once + layer));
 }
