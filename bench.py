@@ -143,7 +143,9 @@ def copy_bandwidth(torch, nbytes: int = 1 << 30, runs: int = 10) -> float:
 
 
 KERNEL_IDS = {"auto": None, "lane": 1, "layer": 2, "deep": 3}
-KERNEL_NAMES = {1: "k_solve_lane", 2: "k_solve_layer", 3: "k_deep_*"}
+# what runs at this file's workloads: the layer kernel's default tile is the stream kernel at
+# all of them, and their deep columns have up to 64 lanes
+KERNEL_NAMES = {1: "k_solve_lane", 2: "k_solve_stream", 3: "k_cascade_*"}
 
 
 def time_path(s, inp, out, precision, steps, warmup, torch, kernel=None, pre=None):

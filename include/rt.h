@@ -64,10 +64,11 @@ typedef int32_t rt_status;
  * is composed per segment and joined by scans over segments: for few, deep
  * columns; several launches on the stream (serving: a launch sequence of its
  * own per request), cols_per_block must be 0.  AUTO picks DEEP for at least 40
- * slabs with at most one column per 2 compute units (FP64: at least 48 to 256
- * slabs, by the lanes per column, and fewer columns), else LAYER.  LAYER with
- * cols_per_block 0 runs a wavefront per set of lanes, with columns split
- * into segments of layers where the grid is small. */
+ * slabs with at most one column per 2 compute units (FP64: where that is also
+ * estimated to be done before LAYER), else LAYER.  LAYER with cols_per_block 0
+ * runs a wavefront per set of lanes, with columns split into segments of layers
+ * where the grid is small, or the layer kernel's own tile where that is
+ * estimated to be done first. */
 #define RT_KERNEL_AUTO  0
 #define RT_KERNEL_LANE  1
 #define RT_KERNEL_LAYER 2

@@ -23,8 +23,9 @@
 // (1 - R c), m7 = kappa T, m0 = kappa R and sigma = kappa S,
 //   F_up(top) = (m7 F_up(bottom) + m0 d + sigma) / w.
 // What bounds it is the latency of one part's chain, about 2500 cycles a layer, and of four
-// launches: 1 x 4096 x 30 FP64 43 us and 16 x 1000 x 30 mixed 56, by the seven launches
-// of rt_deep.hip (which wider columns take) 51 and 81.
+// launches: 1 x 4096 x 30 FP64 44 us and 16 x 1000 x 30 mixed 56, by the seven launches
+// of rt_deep.hip 52 and 82, which wider columns take, sub-layer columns with an odd number of slabs
+// per segment, and columns of a few lanes whose parts would not fit its work buffer (cascade_fits).
 #include "rt_lanes.hpp"
 
 #include <algorithm>

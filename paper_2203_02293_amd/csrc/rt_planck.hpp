@@ -4,7 +4,7 @@
 // above it, each term an FMA and two scalar instructions that build its coefficient:
 // about 100 vector and 170 scalar instructions per (level, bin) of the solve, a
 // third of a wavefront's issue.  Here the integral is one polynomial of degree 11
-// in the cell of x, its coefficients gathered from a table of 2.4 KB in LDS:
+// in the cell of x, its coefficients gathered from a table of 2.6 KB in LDS:
 //   x < 3:  Q(x) / x^3 = 1/3 - x/8 + sum_k B_2k x^2k / ((2k+3)(2k)!)
 //   x >= 3: P(x) e^x, which is x^3 + 3x^2 + 6x + 6 and terms that fall like e^-x
 // Cells: [0, 1), then four per octave up to 64 (the leading bits of x), beyond which

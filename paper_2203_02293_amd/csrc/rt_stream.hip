@@ -12,22 +12,22 @@
 // the elimination in registers, so no item is handed between threads.  The
 // back-substitution records (32 bytes per layer and lane) go through memory, where
 // the L2 still holds most of them when they are read back; the level sums are taken
-// eight levels at a time.  One wavefront is one workgroup: four of them in one kept
-// registers and LDS until the slowest ended (2562 x 40 x 30 x 20 lanes FP64: 2.88 ms by
-// the layer kernel, 1.29 in workgroups of four, 1.10 in single wavefronts, where the
-// FP64 vector units are 80 percent busy; 10242 x 80 x 300 mixed: 7.46 and 4.80 ms).
+// eight levels at a time.  One wavefront is one workgroup (four in one kept registers and
+// LDS until the slowest ended: 17 percent of the time).  2562 x 40 x 30 x 20 lanes FP64: 2.91 ms
+// by the layer kernel, 1.01 here; 10242 x 80 x 300 mixed: 7.42 and 4.23, both at about the
+// rate of memory for inputs and records.
 //
 // Where a grid brings fewer wavefronts than the chip runs (SEG), a wavefront's own
-// chain of dependent FP64 operations (about 2500 cycles per layer) is the time.  Each
+// chain of dependent FP64 operations (about 2 us per layer) is the time.  Each
 // column's layers are then split into S segments from the TOA, one group of lanes each,
 // in the same wavefront (while a column's lanes fill at most half of one) or in several
 // of one workgroup.  Each segment composes the elimination's map over its layers on
 // the way and leaves their coefficients in the records' place; the maps give the state
 // at every segment's top, from which all segments eliminate, and compose their maps of
-// F_up, with which all substitute back (StateMap; about 60 instructions more per layer,
-// and 64 bytes).  162 x 40 x 30 FP64: 50 us by the layer kernel, 92 in one segment, 26 in
-// eight; 2562 x 40 x 30: 140, 121 and 102 in two.  (Handing the elimination from segment
-// to segment instead, without the maps, took 34 us and 138.)
+// F_up, with which all substitute back (StateMap; 64 bytes more per layer and lane).  162 x 40 x
+// 30 FP64: 50 us by the layer kernel, 83 in one segment, 25 in eight; 2562 x 40 x 30: 140, 111
+// and 95 in two.  (Handing the elimination from segment to segment instead, without the
+// maps, took 34 us and 138.)
 #include "rt_lanes.hpp"
 
 #include <algorithm>
@@ -776,25 +776,23 @@ static double stream_time(const Geometry &g, int C, int N, int NB, bool mixed, c
 }
 
 // Segments per column: the least estimated time, where the most segments whose wavefronts
-// the registers hold count a tenth less (us, C x N x NB, FP64 by S; the first is one
-// wavefront per CU or less at S = 1):
-//   162 x 40 x 30      1: 92    2: 58    4: 38    8: 27   16: 30
-//   512 x 40 x 30      1: 93    2: 64    4: 42    8: 35   16: 58
-//   1500 x 40 x 30     1: 94    2: 81    3: 75    4: 65    8: 73
-//   1800 x 40 x 30     1: 95    2: 82    3: 76    4: 88
-//   2562 x 40 x 30     1: 121   2: 102   3: 113
-//   3200 x 40 x 30     1: 124   2: 148
-//   100 x 60 x 300     1: 141   2: 117   3: 88    4: 76    5: 109
-//   300 x 100 x 16     1: 221   4: 79    8: 58   16: 45   20: 62
-//   162 x 20 x 100     4: 32    8: 48 (workgroups of eight wavefronts, one per CU: two rounds)
+// the registers hold count a tenth less (us, C x N x NB by S, FP64; the last column: mixed):
+//   162 x 40 x 30     1: 83    2: 55    4: 36    8: 25   16: 27     1: 73    8: 22   16: 24
+//   512 x 40 x 30     1: 82    2: 58    4: 39    8: 33   16: 54     1: 73    8: 28   16: 46
+//   1500 x 40 x 30    1: 85    2: 74    3: 70    4: 60    8: 69     1: 77    4: 48    8: 57
+//   1800 x 40 x 30    1: 85    2: 75    3: 71    4: 84              1: 77    3: 54    4: 75
+//   2562 x 40 x 30    1: 111   2: 95    3: 106                      1: 88    2: 73    3: 94
+//   3200 x 40 x 30    1: 112   2: 141                               1: 89    2: 124
+//   100 x 60 x 300    1: 125   2: 106   3: 80    4: 67    5: 101    1: 120   4: 57    5: 90
+//   300 x 100 x 16    1: 198   4: 73    8: 53   16: 41   20: 59     1: 168  16: 35   20: 51
+//   162 x 20 x 100    4: 32    8: 47 (workgroups of eight wavefronts, one per CU: two rounds)
 // (5 and 20 give workgroups of five wavefronts, which pack badly on four SIMDs.)  Short
-// segments give less than their hand-over costs: 48 layers take 27 in 8 segments and 29
-// in 16, 60 layers 35 and 31; 20 layers 24 in 4 and 22 in 8; 12 layers 21.7 in 4, 24 in 2;
-// 5 layers 17.8 in 2 and 16.7 in 1.
+// segments give less than their hand-over costs: 48 layers take 26 in 8 segments and 28
+// in 16, 60 layers 34 and 30; 20 layers 23 in 4 and 21 in 8; 12 layers 19.7 in 4, 23 in 2; 5
+// layers 17.6 in 2 and 16.8 in 1.
 // Up to 4 segments, a workgroup takes as many columns as a wavefront holds groups,
-// so that its first wavefront eliminates as it goes (2562 x 40 x 30: 110 to 102,
-// mixed 91 to 76; 3000 x 60 x 16: 121 to 91); with 8 the larger workgroup costs more
-// (162 x 40 x 30: 27 to 32).
+// so that its first wavefront eliminates as it goes (2562 x 40 x 30: 100 to 95, mixed 85 to
+// 73; 3000 x 60 x 16: 112 to 85); with 8 the larger workgroup costs more.
 Geometry stream_geometry(int C, int N, int NB, int NG, bool mixed, const DeviceLimits &dev)
 {
     static constexpr struct {

@@ -70,6 +70,33 @@ def test_lines(shape, kernel, S):
         assert g.PC == S
 
 
+def test_gpu_shapes_reach_every_split():
+    """What the GPU tests of the default tile run: one segment and every split by the stream kernel, and
+    AUTO on both sides of its FP64 line."""
+    from tests.test_gpu_stream import CASES, SEGMENTS, columns
+    for mixed in (False, True):
+        got = [default(C, N, NB, mixed, False) for NB, N, C in SEGMENTS]
+        assert {g.PC for g in got if g.kernel == STREAM} == {1, 2, 3, 4, 8, 16}
+        assert {g.kernel for g in got} == {LAYER, STREAM}
+    for NB, N in CASES:
+        g = default(columns(NB), N, NB, False, False)
+        assert (g.kernel, g.PC) == (STREAM, 1), (NB, N)
+    for shape, kernel in (((64, 87, 30), STREAM), ((64, 88, 30), DEEP), ((65, 88, 30), STREAM), ((3, 47, 40), STREAM),
+                          ((3, 48, 40), DEEP), ((32, 89, 100), DEEP)):
+        assert default(*shape).kernel == kernel, shape
+
+
+def test_bench_names_the_kernels_it_runs():
+    """bench.py's workloads run the kernels that it names: the stream kernel for a default tile, the
+    deep path's four launches for a deep column of up to 64 lanes."""
+    import bench
+    for C, N, NB, NG in ((2562, 40, 30, 1), (2562, 80, 30, 1), (2562, 40, 600, 20), (2562, 80, 600, 20), (10242, 80, 300, 1)):
+        for mixed in (False, True):
+            assert default(C, N, NB, mixed, NG=NG).kernel == STREAM
+    assert default(1, 4096, 30).kernel == DEEP and default(16, 1000, 30, True).kernel == DEEP
+    assert bench.KERNEL_NAMES[2] == "k_solve_stream" and bench.KERNEL_NAMES[3] == "k_cascade_*"
+
+
 def test_reservation_is_the_former_kernels():
     """A default tile asks for the work buffer that the layer or deep kernel asked for at this size, so
     what fitted a budget or the static buffer still does."""
