@@ -295,7 +295,7 @@ __device__ __forceinline__ void solve_tile_stream(ArgsK ap, const int tile)
 
     // Mixed: temperatures at which every bin of the wavefront takes the narrow bins'
     // quadrature; a chunk of such levels needs no edge integrals (10242 x 80 x 300: 380
-    // vector instructions per layer in place of 434).
+    // vector instructions per layer in place of 434; 369 now, with the later steps).
     double narrow_lo = 0.0, narrow_hi = 0.0;
     bool narrow = false;
     if constexpr (MIXED) {
